@@ -328,7 +328,8 @@ int mtx_get_timing(mtx_model* m, mtx_kernel_time* out, int capacity, int* count,
  * the layer, the output tile (rows x columns of the GEMM C[p][q] = sum_k P[p][k] Q[q][k]), the
  * reduction tile, the number of reduction splits (> 1: a second kernel adds the fp32 partial
  * sums), and flags: 1 = interleaved scheduling order, 2 = an operand loaded straight into LDS,
- * 4 = the weight gradient fused with the average + update (mtx_set_fused_update).  Host only, does
+ * 4 = the weight gradient fused with the average + update (mtx_set_fused_update), 8 = a
+ * convolution whose input windows are staged in LDS once for all kernel taps.  Host only, does
  * not synchronise; fills up to `capacity` entries and sets *count to the number of launches. */
 typedef struct {
     char site[32];

@@ -64,6 +64,7 @@ struct LayerPlan {
     bool act_f32;                // stored output is fp32 (always in fp32 mode; logits)
     bool dgrad_col;              // convolution data gradient through col + col2im
     bool dgrad_fused;            // ... with col tile and col2im in one kernel (dgrad_fused.hip)
+    HaloPlan fhalo, bhalo;       // forward / data gradient over LDS windows (conv_halo.hip)
     bool need_dx;                // the data gradient of this layer's input is computed
     bool nhwc;                   // stored output is NHWC (convolution and pooling layers)
     int perm_c, perm_hw;         // fully connected after a spatial layer: input in (h, w, c)
@@ -114,7 +115,9 @@ ConvGeom proj_geom(const LayerPlan& lp, const LayerPlan& sp, int N)
     return ConvGeom{N, sp.oc, sp.oh, sp.ow, lp.oc, lp.oh, lp.ow, 1, lp.s, 0, 1};
 }
 
-int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl)
+// halo = false: without the convolutions over LDS windows (their padded weight layouts may need a
+// little more workspace than a caller has).
+int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true)
 {
     if (!d) return fail(MTX_EINVAL, "desc is NULL");
     if (!d->layers || d->n_layers < 1) return fail(MTX_EINVAL, "the network has no layers");
@@ -342,10 +345,21 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl)
             }
         } else if (lp.kind == MTX_CONV) {
             j.g = lp.g; j.cg = lp.c / lp.g; j.og = lp.oc / lp.g; j.KK = lp.k * lp.k;
+            const ConvGeom gb{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
+            auto halo_job = [&](const HaloPlan& h, int kind) {
+                PrepJob q = j;
+                q.kind = kind;
+                q.n = (int)h.w_elems;
+                q.Cp = h.ckg; q.K = h.ks; q.RUN = h.PB;
+                return add_job(q);
+            };
+            if (halo) lp.fhalo = conv_halo_plan(pl.dt, gb, false);
             j.kind = PREP_CONV_F;
-            lp.fw_off = add_job(j);
-            if (lp.need_dx) {
-                ConvGeom gb{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
+            lp.fw_off = lp.fhalo.ok ? halo_job(lp.fhalo, PREP_HALO_F) : add_job(j);
+            if (halo && lp.need_dx) lp.bhalo = conv_halo_plan(pl.dt, gb, true);
+            if (lp.bhalo.ok) {
+                lp.bw_off = halo_job(lp.bhalo, PREP_HALO_D);
+            } else if (lp.need_dx) {
                 lp.dgrad_col = conv_dgrad_use_col(gb);
                 lp.dgrad_fused = lp.dgrad_col && conv_dgrad_fused_ok(gb, pl.dt);
                 j.kind = lp.dgrad_col ? PREP_CONV_C : PREP_CONV_D;
@@ -416,9 +430,10 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl)
             ConvGeom gb{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
             ConvGeom gs = gb;
             gs.N = pl.Nb;
-            dims[nd++] = lp.run ? conv_fwd_run_dims(pl.dt, gb, lp.rg) : conv_fwd_dims(pl.dt, gb);
+            if (!lp.fhalo.ok)
+                dims[nd++] = lp.run ? conv_fwd_run_dims(pl.dt, gb, lp.rg) : conv_fwd_dims(pl.dt, gb);
             if (lp.need_dx) {
-                if (lp.dgrad_fused) {
+                if (lp.dgrad_fused || lp.bhalo.ok) {
                     // no col buffer and no split reduction
                 } else if (lp.dgrad_col) {
                     dims[nd++] = conv_dgrad_col_dims(pl.dt, gb);
@@ -891,6 +906,11 @@ static int init_model(const mtx_model_desc* desc, int R, int shard_batch, uint64
     Plan pl;
     int rc = make_plan(desc, R, shard_batch, pl);
     if (rc) return rc;
+    const size_t ws_have = static_ws ? kStaticScratchBytes : bufs->workspace_bytes;
+    if (pl.ws_bytes > ws_have) {
+        rc = make_plan(desc, R, shard_batch, pl = Plan(), false);
+        if (rc) return rc;
+    }
     if (!bufs->w || !bufs->v || !bufs->grads || !bufs->grad_avg ||
         (!static_ws && !bufs->workspace))
         return fail(MTX_EINVAL, "a model buffer is NULL");
@@ -1193,6 +1213,9 @@ static int enqueue_step(mtx_model* m, const float* x, const int32_t* labels, flo
         } else if (lp.kind == MTX_CONV) {
             ConvGeom g{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
             HIP_TRY(launch_site(m, "fwd", (int)l, s, [&] {
+                        if (lp.fhalo.ok)
+                            return conv_halo(g, lp.fhalo, false, in, fwd_w(lp), bias, lp.relu,
+                                             nullptr, out, s);
                         return lp.run ? conv_fwd_run(dt, g, lp.rg, in, fwd_w(lp), bias, out,
                                                      lp.act_f32, lp.relu, partial, s)
                                       : conv_fwd(dt, g, in, fwd_w(lp), bias, out, lp.act_f32,
@@ -1348,6 +1371,9 @@ static int enqueue_step(mtx_model* m, const float* x, const int32_t* labels, flo
                 ConvGeom g{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
                 float* col = reinterpret_cast<float*>(ws + pl.col_off);
                 HIP_TRY(launch_site(m, "dgrad", l, s, [&] {
+                            if (lp.bhalo.ok)
+                                return conv_halo(g, lp.bhalo, true, dy, bwd_w(lp), nullptr, false,
+                                                 mask, dx, s);
                             if (lp.dgrad_fused)
                                 return conv_dgrad_fused(g, static_cast<const float*>(dy),
                                                         m->w + lp.w_off, static_cast<float*>(dx),

@@ -173,6 +173,12 @@ void prep_fill_divisors(PrepJob& j)
         j.f0 = make_fastdiv((unsigned)j.RUN);
         j.f1 = make_fastdiv((unsigned)j.Cp);
         break;
+    case PREP_HALO_F:
+    case PREP_HALO_D:
+        j.f0 = make_fastdiv((unsigned)j.K);
+        j.f1 = make_fastdiv((unsigned)j.Cp);
+        j.f2 = make_fastdiv((unsigned)j.RUN);
+        break;
     default:
         break;
     }

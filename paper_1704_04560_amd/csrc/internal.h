@@ -155,6 +155,7 @@ void timing_split(hipStream_t s, const char* part);
 constexpr int kGemmInterleaved = 1;  // the interleaved scheduling order of igemm_kernel
 constexpr int kGemmDirectLds = 2;    // an operand loaded straight into LDS (igemm_direct_kernel)
 constexpr int kGemmFusedUpdate = 4;  // the weight gradient fused with the average + update
+constexpr int kGemmHalo = 8;         // input windows in LDS, read by every tap (conv_halo.hip)
 void note_gemm(int fp, int fq, int bk, int splits, int flags);
 
 // elementwise.hip
@@ -167,6 +168,8 @@ enum PrepKind {
     PREP_CONV_C,     // Wc
     PREP_FC_PERM,    // W[o][(c, h, w)] -> W[o][(h, w, c)]
     PREP_CONV_RUN,   // Wr[co][u][j] of a first-layer convolution over a padded input
+    PREP_HALO_F,     // fragment-major weights of conv_halo, forward
+    PREP_HALO_D,     // ... data gradient
 };
 struct PrepJob {
     int kind;
@@ -174,7 +177,8 @@ struct PrepJob {
     long long src;     // element offset in the fp32 weights
     long long dst;     // element offset in the prepared buffer
     int g, cg, og, KK; // convolution: groups, channels per group in / out, K*K
-    int C, HW, IN;     // fully connected permutation; C, Cp, K, RUN of a padded first layer
+    int C, HW, IN;     // fully connected permutation; C, Cp, K, RUN of a padded first layer;
+                       // Cp, K, RUN = granules per tap, k steps, row blocks (halo)
     int Cp, K, RUN;
     int block0;        // first block of this job in the launch
     FastDiv f0, f1, f2;
@@ -314,5 +318,22 @@ constexpr size_t kDxMaxLds = 80 * 1024;
 bool conv_dgrad_fused_ok(const ConvGeom& g, int dt);
 hipError_t conv_dgrad_fused(const ConvGeom& g, const float* dy, const float* w, float* dx,
                             const void* mask, bool mask_f32, hipStream_t s);
+
+// conv_halo.hip: bf16 stride-1 convolution forward and data gradient with the
+// input window of an output tile held in LDS; the products and their order are those of the
+// implicit GEMM, so the results are the same bits.  conv_halo_plan tells whether a layer takes it
+// (ok) and how its weights are laid out (w_elems elements, PREP_HALO_F / PREP_HALO_D).
+struct HaloPlan {
+    bool ok;
+    int shape;                // block shape (index into the kernel's list)
+    int tile;                 // outputs of a block
+    int ckg, ks, PB;          // 8-channel granules, k steps of 32, blocks of 16 output rows
+    int stride, zero_off;     // LDS bytes per position, of the zero position
+    int lds;                  // LDS bytes of the window (and of the output tile)
+    long long w_elems;
+};
+HaloPlan conv_halo_plan(int dt, const ConvGeom& g, bool bwd);
+hipError_t conv_halo(const ConvGeom& g, const HaloPlan& h, bool bwd, const void* x, const void* w,
+                     const float* bias, bool relu, const void* mask, void* y, hipStream_t s);
 
 }  // namespace mtx

@@ -42,6 +42,18 @@ __device__ __forceinline__ int prep_src(const PrepJob& j, unsigned d)
         if (v >= (unsigned)j.K || ci >= (unsigned)j.C) return -1;
         return (((int)co * j.C + (int)ci) * j.K + (int)u) * j.K + (int)v;
     }
+    case PREP_HALO_F:
+    case PREP_HALO_D: {  // d = ((g*PB + pb)*ks + k)*512 + lane*8 + e
+        const unsigned e = d & 7u, lane = (d >> 3) & 63u;
+        const unsigned r1 = d >> 9, r2 = prep_fdivu(j.f0, r1), k = r1 - r2 * (unsigned)j.K;
+        const unsigned g = prep_fdivu(j.f2, r2), pb = r2 - g * (unsigned)j.RUN;
+        const unsigned gi = k * 4u + (lane >> 4), tap = prep_fdivu(j.f1, gi);
+        const unsigned p = pb * 16u + (lane & 15u), c = (gi - tap * (unsigned)j.Cp) * 8u + e;
+        const bool fwd = j.kind == PREP_HALO_F;
+        if (tap >= (unsigned)j.KK || p >= (unsigned)(fwd ? j.og : j.cg)) return -1;
+        const unsigned co = fwd ? p : c, ci = fwd ? c : p;
+        return (int)((g * (unsigned)j.og + co) * (unsigned)j.cg + ci) * j.KK + (int)tap;
+    }
     case PREP_FC_PERM: {  // d = o*IN + hw*C + c
         const unsigned o = prep_fdivu(j.f0, d), r = d - o * (unsigned)j.IN;
         const unsigned hw = prep_fdivu(j.f1, r), c = r - hw * (unsigned)j.C;

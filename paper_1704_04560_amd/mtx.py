@@ -61,7 +61,7 @@ class mtx_launch_info(C.Structure):
                 ("flags", C.c_int)]
 
 
-MTX_GEMM_INTERLEAVED, MTX_GEMM_DIRECT_LDS, MTX_GEMM_FUSED_UPDATE = 1, 2, 4
+MTX_GEMM_INTERLEAVED, MTX_GEMM_DIRECT_LDS, MTX_GEMM_FUSED_UPDATE, MTX_GEMM_HALO = 1, 2, 4, 8
 
 
 class mtx_buffers(C.Structure):

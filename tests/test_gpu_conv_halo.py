@@ -1,0 +1,80 @@
+"""GPU parity of the convolutions that hold their input windows in LDS (bf16) against the oracle,
+and against the implicit GEMM bit for bit: block shapes, channel counts that are not multiples of
+32 or 64, output channels off every vector width, ragged reduction steps, unpadded and grouped
+layers, tiles that cross images, whole-image tiles."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1704_04560_amd import mtx
+from paper_1704_04560_amd import workloads as wl
+from tests.test_gpu_train_step import run_case
+
+pytestmark = pytest.mark.gpu
+
+# name: input shape, layers, shards, shard batch, the launches (site, layer, tile rows) expected
+CASES = {
+    # 16 channels, scalar stores (20 and 18 outputs), 5x5 windows; groups of 24 channels whose 27
+    # granules leave a ragged k step
+    "narrow": ((3, 41, 53), (wl.conv(16, 3, pad=1, relu=True), wl.conv(20, 5, pad=2, relu=True),
+                             wl.conv(48, 1, relu=True), wl.conv(18, 3, pad=1, groups=2, relu=True),
+                             wl.maxpool(3, 2), wl.fc(5)),
+               3, 8, {("fwd", 1, 32), ("fwd", 3, 32)}),
+    # 72 channels, unpadded (the data gradient's windows reach over the whole border), 56 outputs
+    "unpadded": ((3, 37, 43), (wl.conv(16, 3, pad=1, relu=True), wl.conv(72, 3, relu=True),
+                               wl.conv(56, 3, pad=1, relu=True), wl.maxpool(2, 2), wl.fc(4)),
+                 2, 17, {("fwd", 1, None), ("dgrad", 1, None), ("fwd", 2, None), ("dgrad", 2, None)}),
+    # 96-row tiles
+    "rows96": ((16, 37, 43), (wl.conv(92, 3, relu=True), wl.conv(16, 2), wl.maxpool(3, 3), wl.fc(4)),
+               4, 21, {("fwd", 0, 96), ("dgrad", 1, 96)}),
+    # 8 x 8 images: every tile crosses images; 2x2 and 7x7 kernels, more padding than the window
+    # needs
+    "small": ((8, 8, 8), (wl.conv(40, 2, relu=True), wl.conv(32, 7, pad=3, relu=True),
+                          wl.conv(48, 3, pad=4), wl.fc(3)), 2, 520,
+              {("fwd", 0, 64), ("dgrad", 1, 64), ("fwd", 2, 64), ("dgrad", 2, 32)}),
+    # 13 x 13 images, one per block: 192 and 384 rows in eight waves, 192 in four
+    "image": ((64, 13, 13), (wl.conv(192, 3, pad=1, relu=True), wl.conv(384, 3, pad=1, groups=2),
+                             wl.fc(3)), 2, 200,
+              {("fwd", 0, 192), ("fwd", 1, 192), ("dgrad", 1, 96)}),
+    "wide": ((64, 13, 13), (wl.conv(256, 3, pad=1, relu=True), wl.conv(384, 3, pad=1), wl.fc(3)), 1,
+             200, {("fwd", 1, 384), ("dgrad", 1, 256)}),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_window_convolutions_match_oracle(name):
+    shape, layers, R, Nb, expected = CASES[name]
+    net = wl.Net("halo-" + name, shape, layers, wl.BF16, "normal")
+    model = mtx.Model(shape, wl.layer_tuples(net), wl.BF16, R, Nb, seed=1)
+    x, y = wl.make_batch(net, R * Nb, seed=1)
+    model.train_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.01, 0.9)
+    torch.cuda.synchronize()
+    seen = {(l["site"], l["layer"]): l["tile_rows"] for l in mtx.mtx_get_launches(model.handle)
+            if l["flags"] & mtx.MTX_GEMM_HALO}
+    print(f"[launches] {name}: {seen}", flush=True)
+    model.close()
+    for site, layer, rows in expected:
+        assert (site, layer) in seen and rows in (None, seen[(site, layer)]), (site, layer, rows, seen)
+    run_case("halo-" + name, net, R, Nb, 1, 3, 0.01, 0.9)
+
+
+def test_window_convolution_keeps_infinities_apart():
+    """One infinite input value: only the outputs whose window holds it may differ from a run
+    with that value zero (the zero weights of padded reduction granules meet zero inputs)."""
+    # 24 channels x 9 taps leave a padded granule
+    layers = (wl.conv(24, 1), wl.conv(16, 3, pad=1), wl.fc(3))
+    net = wl.Net("halo-inf", (24, 50, 50), layers, wl.BF16, "normal")
+    x, y = wl.make_batch(net, 24, seed=2)
+    outs = []
+    for value in (0.0, np.inf):
+        x[3, 2, 20, 30] = value
+        model = mtx.Model(net.in_shape, wl.layer_tuples(net), wl.BF16, 2, 12, seed=1)
+        model.train_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.0, 0.0)
+        assert any(l["flags"] & mtx.MTX_GEMM_HALO and l["site"] == "fwd"
+                   for l in mtx.mtx_get_launches(model.handle))
+        outs.append(model.layer_output(1).reshape(24, 16, 50, 50))
+        model.close()
+    differ = np.argwhere(outs[0] != outs[1])
+    assert len(differ)
+    assert (differ[:, 0] == 3).all()
+    assert (np.abs(differ[:, 2] - 20) <= 1).all() and (np.abs(differ[:, 3] - 30) <= 1).all()
