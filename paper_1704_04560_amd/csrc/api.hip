@@ -65,6 +65,7 @@ struct LayerPlan {
     bool dgrad_col;              // convolution data gradient through col + col2im
     bool dgrad_fused;            // ... with col tile and col2im in one kernel (dgrad_fused.hip)
     HaloPlan fhalo, bhalo;       // forward / data gradient over LDS windows (conv_halo.hip)
+    HaloWPlan whalo;             // weight gradient over LDS windows (conv_halo_wgrad.hip)
     bool need_dx;                // the data gradient of this layer's input is computed
     bool nhwc;                   // stored output is NHWC (convolution and pooling layers)
     int perm_c, perm_hw;         // fully connected after a spatial layer: input in (h, w, c)
@@ -357,6 +358,9 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true
             j.kind = PREP_CONV_F;
             lp.fw_off = lp.fhalo.ok ? halo_job(lp.fhalo, PREP_HALO_F) : add_job(j);
             if (halo && lp.need_dx) lp.bhalo = conv_halo_plan(pl.dt, gb, true);
+            ConvGeom gs = gb;
+            gs.N = pl.Nb;
+            if (halo) lp.whalo = conv_halo_wgrad_plan(pl.dt, gs, pl.R);
             if (lp.bhalo.ok) {
                 lp.bw_off = halo_job(lp.bhalo, PREP_HALO_D);
             } else if (lp.need_dx) {
@@ -423,6 +427,7 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true
         // dims is the weight gradient)
         GemmDims dims[3];
         int nd = 0;
+        size_t wgrad_partial = 0;
         if (lp.kind == MTX_CONV && lp.direct) {
             ConvGeom gs{pl.Nb, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
             max_first = std::max(max_first, first_conv_partial_floats(gs, pl.R));
@@ -442,8 +447,11 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true
                     dims[nd++] = conv_dgrad_dims(pl.dt, gb);
                 }
             }
-            dims[nd++] = lp.run ? conv_wgrad_run_dims(pl.dt, gs, lp.rg, pl.R)
-                                : conv_wgrad_dims(pl.dt, gs, pl.R);
+            if (lp.whalo.ok)
+                wgrad_partial = conv_halo_wgrad_partial(lp.whalo, pl.R);
+            else
+                dims[nd++] = lp.run ? conv_wgrad_run_dims(pl.dt, gs, lp.rg, pl.R)
+                                    : conv_wgrad_dims(pl.dt, gs, pl.R);
         } else if (lp.kind == MTX_FC) {
             dims[nd++] = fc_fwd_dims(pl.dt, pl.B, (int)lp.in_elems, lp.oc);
             if (lp.need_dx) dims[nd++] = fc_dgrad_dims(pl.dt, pl.B, (int)lp.in_elems, lp.oc);
@@ -462,12 +470,12 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true
         }
         for (int k = 0; k < nd; ++k) {
             const size_t pz = partial_elems(pl.dt, dims[k]);
-            const bool wgrad = k == nd - 1;
-            size_t& mx = wgrad ? max_partial_w : max_partial;
-            if (pz > mx) mx = pz;
-            // the first parameter layer's weight gradient runs on the caller's stream
-            if (wgrad && (int)i == pl.first_param && pz > max_partial) max_partial = pz;
+            if (k == nd - 1 && !lp.whalo.ok) wgrad_partial = pz;
+            else max_partial = std::max(max_partial, pz);
         }
+        max_partial_w = std::max(max_partial_w, wgrad_partial);
+        // the first parameter layer's weight gradient runs on the caller's stream
+        if ((int)i == pl.first_param) max_partial = std::max(max_partial, wgrad_partial);
         if (lp.w_len) pl.n_wgrad += 1;
         if (lp.w_len && lp.kind == MTX_ADDP) {
             const double macs = (double)pl.B * lp.oh * lp.ow * lp.oc * pl.L[lp.src].oc;
@@ -1360,6 +1368,9 @@ static int enqueue_step(mtx_model* m, const float* x, const int32_t* labels, flo
         } else if (lp.kind == MTX_CONV) {
             ConvGeom gs{pl.Nb, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
             HIP_TRY(launch_site(m, "wgrad", l, sw, [&] {
+                        if (lp.whalo.ok)
+                            return conv_halo_wgrad(gs, lp.whalo, pl.R, in_l, dy, m->grads, ld,
+                                                   (long long)lp.w_off, part_wg, sw);
                         return lp.run ? conv_wgrad_run(dt, gs, lp.rg, pl.R, in_l, dy, m->grads, ld,
                                                        (long long)lp.w_off, (long long)lp.b_off,
                                                        part_wg, sw)

@@ -333,6 +333,21 @@ struct HaloPlan {
     long long w_elems;
 };
 HaloPlan conv_halo_plan(int dt, const ConvGeom& g, bool bwd);
+// conv_halo_wgrad.hip: bf16 weight and bias gradient of R shards of g.N images (stride 1 or 2,
+// 2x2, 3x3, 5x5 and 7x7 kernels) over input windows held in LDS; partial: fp32 scratch of
+// conv_halo_wgrad_partial() elements.  The bias follows the weights in a gradient row.
+struct HaloWPlan {
+    bool ok;
+    int fa, ng;               // 16-channel fragments of dy, kernel-row groups per wave
+    int cot, ubs, ngroups;    // output channel tiles, group tiles, groups (ci16, u)
+    int ckg, stride, Hp, Wp, xlds;
+    int tiles, tps, splits;   // 128-position tiles of a shard, per split, splits
+    long long n, ld;          // values of a gradient row, padded partial row
+};
+HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R);
+size_t conv_halo_wgrad_partial(const HaloWPlan& h, int R);
+hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const void* x, const void* dy,
+                           float* grads, long long ld, long long w_off, float* partial, hipStream_t s);
 hipError_t conv_halo(const ConvGeom& g, const HaloPlan& h, bool bwd, const void* x, const void* w,
                      const float* bias, bool relu, const void* mask, void* y, hipStream_t s);
 

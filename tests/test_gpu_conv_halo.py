@@ -78,3 +78,34 @@ def test_window_convolution_keeps_infinities_apart():
     assert len(differ)
     assert (differ[:, 0] == 3).all()
     assert (np.abs(differ[:, 2] - 20) <= 1).all() and (np.abs(differ[:, 3] - 30) <= 1).all()
+
+
+# name: input shape, layers, shards, shard batch, the layers whose weight gradient takes windows
+WGRAD_CASES = {
+    # channel counts on 2- and 8-byte loads, a 2x2 kernel, groups, 32-channel output tiles
+    "odd": ((3, 33, 31), (wl.conv(15, 3, pad=1, relu=True), wl.conv(20, 3, pad=1, relu=True),
+                          wl.conv(36, 5, pad=2, groups=2, relu=True), wl.conv(12, 2),
+                          wl.maxpool(3, 3), wl.fc(3)), 4, 20, {1, 2, 3}),
+    # a first layer of 8 channels with a 7x7 kernel, stride 2, an unpadded 5x5 layer
+    "strided": ((8, 24, 24), (wl.conv(16, 7, pad=3, relu=True), wl.conv(136, 3, stride=2, pad=1, relu=True),
+                              wl.conv(64, 5, relu=True), wl.maxpool(2, 2), wl.fc(5)), 32, 5, {0, 1, 2}),
+    # one split: the rows are written straight into gradient rows that start off 16 bytes
+    "direct": ((3, 8, 8), (wl.bn(), wl.conv(128, 3, pad=1, relu=True), wl.conv(256, 3, pad=1), wl.fc(3)),
+               64, 2, {2}),
+}
+
+
+@pytest.mark.parametrize("name", sorted(WGRAD_CASES))
+def test_window_weight_gradients_match_oracle(name):
+    shape, layers, R, Nb, expected = WGRAD_CASES[name]
+    net = wl.Net("halo-wgrad-" + name, shape, layers, wl.BF16, "normal")
+    model = mtx.Model(shape, wl.layer_tuples(net), wl.BF16, R, Nb, seed=1)
+    x, y = wl.make_batch(net, R * Nb, seed=1)
+    model.train_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.01, 0.9)
+    torch.cuda.synchronize()
+    seen = {l["layer"]: (l["tile_rows"], l["splits"]) for l in mtx.mtx_get_launches(model.handle)
+            if l["flags"] & mtx.MTX_GEMM_HALO and l["site"] == "wgrad"}
+    print(f"[launches] {name}: {seen}", flush=True)
+    model.close()
+    assert expected <= set(seen), (expected, seen)
+    run_case("halo-wgrad-" + name, net, R, Nb, 1, 3, 0.01, 0.9)
