@@ -327,9 +327,18 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true
         j.n = (int)lp.w_len;
         j.src = (long long)lp.w_off;
         if (lp.kind == MTX_CONV && lp.run) {
-            j.kind = PREP_CONV_RUN;
-            j.n = lp.oc * lp.k * lp.rg.RUN;
-            j.C = lp.c; j.Cp = lp.rg.Cp; j.K = lp.k; j.RUN = lp.rg.RUN;
+            const ConvGeom gb{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
+            if (halo) lp.fhalo = conv_halo_run_plan(pl.dt, gb, lp.rg);
+            if (lp.fhalo.ok) {
+                j.kind = PREP_HALO_RUN;
+                j.n = (int)lp.fhalo.w_elems;
+                j.og = lp.oc; j.C = lp.c; j.HW = lp.rg.Cp; j.IN = lp.k;
+                j.Cp = lp.fhalo.ckg; j.K = lp.fhalo.ks; j.RUN = lp.fhalo.PB;
+            } else {
+                j.kind = PREP_CONV_RUN;
+                j.n = lp.oc * lp.k * lp.rg.RUN;
+                j.C = lp.c; j.Cp = lp.rg.Cp; j.K = lp.k; j.RUN = lp.rg.RUN;
+            }
             lp.fw_off = add_job(j);
         } else if (lp.kind == MTX_CONV && lp.direct) {
             continue;  // the direct kernels read the fp32 weights (and round them as they load)
@@ -1221,6 +1230,9 @@ static int enqueue_step(mtx_model* m, const float* x, const int32_t* labels, flo
         } else if (lp.kind == MTX_CONV) {
             ConvGeom g{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
             HIP_TRY(launch_site(m, "fwd", (int)l, s, [&] {
+                        if (lp.fhalo.ok && lp.run)
+                            return conv_halo_run(g, lp.rg, lp.fhalo, in, fwd_w(lp), bias, lp.relu,
+                                                 out, s);
                         if (lp.fhalo.ok)
                             return conv_halo(g, lp.fhalo, false, in, fwd_w(lp), bias, lp.relu,
                                              nullptr, out, s);

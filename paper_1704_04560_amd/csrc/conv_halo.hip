@@ -22,7 +22,10 @@
 // channels, batch 256 (115 GFLOP) 152 -> 110 us forward, 193 -> 158 us data gradient; 13 x 13,
 // 256 -> 384 93 -> 70 and 95 -> 82 us, 2 groups of 192 -> 192 83 -> 58 and 88 -> 60 us; 32 x 32,
 // 64 -> 64, batch 512 68 -> 53 and 87 -> 57 us; 8 x 8, 256 -> 256 56 -> 41 and 58 -> 40 us.
-// Strided layers keep the implicit GEMM (16 x 16 outputs, 3 x 3 stride 2, 128 channels: 39 us
+// A padded first layer (conv_fwd_run) takes the same kernel at any stride: its window is whole rows
+// of the padded input and a reduction granule lies at a fixed offset from an output's origin.
+// AlexNet step (11 x 11, stride 4) 2370 -> 2338 us, CIFAR 828 -> 814, residual block 558 -> 550.
+// Other strided layers keep the implicit GEMM (16 x 16 outputs, 3 x 3 stride 2, 128 channels: 39 us
 // against 41 here, whose window holds four times the positions), and so do channel counts that
 // are not whole 16-byte granules (their reduction steps would hold other products).
 #include <algorithm>
@@ -42,15 +45,19 @@ struct HaloArgs {
     int cg, P, Q, relu;
     int tile;            // outputs of a block (at most its columns)
     int ckg, ks, stride, PT, PB, zero_off, tab_off, vout;
+    int S, Hp, row;      // padded first-layer input: stride, rows per image, elements per row
     FastDiv fd_ohw, fd_ow, fd_ckg;
 };
 
 // BWD: y = data gradient, input rows h + PD - u instead of h - PD + u.  NW waves, WP of
-// them along the output channels.  C64: channels per group a multiple of 64, so that a tap is
-// an even number of whole k steps.
-template <int NW, int FP, int WP, int FQ, bool BWD, bool C64>
+// them along the output channels.  MODE: M_C64: channels per group a multiple of 64, so that a
+// tap is an even number of whole k steps; M_RUN: the padded first-layer input (conv_fwd_run),
+// whose reduction runs along window rows.
+enum { M_ANY = 0, M_C64 = 1, M_RUN = 2 };
+template <int NW, int FP, int WP, int FQ, bool BWD, int MODE>
 __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kernel(const HaloArgs a)
 {
+    constexpr bool C64 = MODE == M_C64, RUN = MODE == M_RUN;
     constexpr int NT = 64 * NW, WQ = NW / WP, BP = 16 * FP * WP, BQ = 16 * FQ * WQ;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     int2* tab = reinterpret_cast<int2*>(lds + a.tab_off);
@@ -74,9 +81,17 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
     const unsigned n0 = fdiv(a.fd_ohw, (unsigned)q0), n1 = fdiv(a.fd_ohw, (unsigned)q1);
     const unsigned h0 = fdiv(a.fd_ow, (unsigned)q0 - n0 * (unsigned)(a.OH * a.OW));
     const unsigned h1 = fdiv(a.fd_ow, (unsigned)q1 - n1 * (unsigned)(a.OH * a.OW));
-    const int r0 = (int)n0 * a.H + min(max(row_lo((int)h0), 0), a.H - 1);
-    const int r1 = (int)n1 * a.H + min(max(row_lo((int)h1) + a.K - 1, 0), a.H - 1);
-    const int pos0 = r0 * a.W, ngran = (r1 - r0 + 1) * a.W * a.ckg;
+    int r0, r1;
+    if constexpr (RUN) {
+        r0 = (int)n0 * a.Hp + (int)h0 * a.S;
+        r1 = (int)n1 * a.Hp + (int)h1 * a.S + a.K - 1;
+    } else {
+        r0 = (int)n0 * a.H + min(max(row_lo((int)h0), 0), a.H - 1);
+        r1 = (int)n1 * a.H + min(max(row_lo((int)h1) + a.K - 1, 0), a.H - 1);
+    }
+    // (a padded row's last window may read past the row, against zero weights: one more run)
+    const int pos0 = r0 * a.W;
+    const int ngran = RUN ? (r1 - r0 + 1) * (a.row / 8) + a.ckg : (r1 - r0 + 1) * a.W * a.ckg;
 
     const __amdgpu_buffer_rsrc_t bx = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<bf16_t*>(a.x), (short)0, (int)a.x_bytes, (int)kRsrcWord3);
@@ -94,21 +109,25 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
         for (int s = 0; s < NS; ++s) {
             const int t = t0 + s * NT;
             const unsigned pos = fdiv(a.fd_ckg, (unsigned)t), g = (unsigned)t - pos * (unsigned)a.ckg;
-            const int off = (pos0 + (int)pos) * a.C + grp * a.cg + (int)g * 8;
+            const int off = RUN ? r0 * a.row + t * 8 : (pos0 + (int)pos) * a.C + grp * a.cg + (int)g * 8;
             v[s] = __builtin_amdgcn_raw_buffer_load_b128(bx, t < ngran ? off * 2 : (int)kOOB, 0, 0);
-            dst[s] = (int)(pos * (unsigned)a.stride + g * 16);
+            dst[s] = RUN ? t * 16 : (int)(pos * (unsigned)a.stride + g * 16);
         }
 #pragma unroll
         for (int s = 0; s < NS; ++s)
             if (t0 + s * NT < ngran) *reinterpret_cast<u32x4*>(lds + dst[s]) = v[s];
     }
     // the zero position that taps in the padding read
-    if (tid < a.ckg) *reinterpret_cast<u32x4*>(lds + a.zero_off + tid * 16) = u32x4{0u, 0u, 0u, 0u};
+    if (tid < (RUN ? 1 : a.ckg)) *reinterpret_cast<u32x4*>(lds + a.zero_off + tid * 16) = u32x4{0u, 0u, 0u, 0u};
     // table of the reduction granules i = (u, v, c8) in ascending order: LDS byte offset from an
     // output's origin, and the two validity bits the tap needs
-    const int ngr = a.K * a.K * a.ckg;
+    const int ngr = (RUN ? a.K : a.K * a.K) * a.ckg;
     for (int i = tid; !C64 && i < (a.ks + 2) * 4; i += NT) {
         const int tap = (int)fdiv(a.fd_ckg, (unsigned)i), c8 = i - tap * a.ckg, u = tap / a.K, v = tap - u * a.K;
+        if constexpr (RUN) {  // i = (u, c8): window row u, run granule c8
+            tab[i] = i < ngr ? make_int2(tap * a.row * 2 + c8 * 16, 0) : make_int2(0, (int)0x80000000u);
+            continue;
+        }
         const int o = (u * a.W + v) * a.stride;
         // (granules past the last tap: no output has bit 31, so they read zeros)
         tab[i] = i < ngr ? make_int2((BWD ? -o : o) + c8 * 16, 1 << u | 1 << (8 + v))
@@ -122,6 +141,11 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
         const unsigned qq = q <= q1 ? q : q0;
         const unsigned n = fdiv(a.fd_ohw, qq), r = qq - n * (unsigned)(a.OH * a.OW);
         const unsigned oh = fdiv(a.fd_ow, r), ow = r - oh * (unsigned)a.OW;
+        if constexpr (RUN) {
+            base[j] = (((int)n * a.Hp + (int)oh * a.S - r0) * a.row + (int)ow * a.S * a.C) * 2;
+            ok[j] = 0;
+            continue;
+        }
         const int h = BWD ? (int)oh + a.PD : (int)oh - a.PD;
         const int w = BWD ? (int)ow + a.PD : (int)ow - a.PD;
         base[j] = (((int)n * a.H + h) * a.W + w - pos0) * a.stride;
@@ -295,6 +319,52 @@ constexpr Shape kShapes[] = {{8, 1, 2, 4, 2, 1.6},  {8, 2, 2, 4, 2, 1.15},  {8, 
                              {4, 3, 4, 11, 2, 0.78}, {8, 2, 8, 11, 1, 0.86}, {8, 3, 8, 11, 1, 0.76}};
 constexpr int kCuLds = 160 * 1024, kLdsUnit = 1280;
 
+// Chooses the block shape of a convolution of N images with img outputs each (OW per row), P
+// output channels in each of G groups and ks k steps: rows(q0, q1) gives the window of a range
+// of outputs in rows of rowb LDS bytes, extra more bytes belong to it, tab bytes follow it.
+template <class Rows>
+void choose_shape(HaloPlan& h, long long Q, int img, int P, int G, long long rowb, long long extra,
+                  long long tab, Rows&& rows_of)
+{
+    double best = 0;
+    for (int i = 0; i < (int)(sizeof kShapes / sizeof kShapes[0]); ++i) {
+        const Shape& s = kShapes[i];
+        const int BP = 16 * s.fp * s.wp, BQ = 16 * s.fq * (s.nw / s.wp);
+        // whole images where they fit and fill the columns, else BQ outputs in a row
+        const int whole = BQ / img * img, tile = whole * 10 >= BQ * 9 ? whole : BQ;
+        // the largest input window of any output tile (tiles repeat their place in an image)
+        long long rows = 0;
+        const long long period = (long long)img / std::__gcd(tile, img) * tile;
+        for (long long q0 = 0; q0 < std::min(Q, period); q0 += tile)
+            rows = std::max<long long>(rows, rows_of(q0, std::min<long long>(q0 + tile, Q) - 1));
+        const long long win = rows * rowb + extra;
+        const long long body = std::max(win, (long long)BQ * (BP + 8) * 2), lds = body + tab;
+        if (lds > kCuLds) continue;
+        const long long blocks = (Q + tile - 1) / tile * halo_cdiv(P, BP) * G;
+        // (fewer blocks than this leave a quarter of the compute units idle, where the implicit
+        // GEMM's smaller tiles do not)
+        if (blocks < 192) continue;
+        // products per SIMD on the busiest compute unit; the fewer waves a SIMD has, the more of
+        // the fragment reads' latency shows, and one block per unit overlaps no staging
+        const int res = std::min<int>(s.res, (int)(kCuLds / ((lds + kLdsUnit - 1) / kLdsUnit * kLdsUnit)));
+        const long long n = (blocks + 255) / 256;
+        const int waves = (int)std::min<long long>(res, n) * s.nw / 4;
+        const double cost = (double)n * s.nw / 4 * s.fp * s.fq * s.weight *
+                            (waves < 2 ? 1.35 : waves < 3 ? 1.07 : 1.0) * (n == 1 ? 1.05 : 1.0);
+        if (best == 0 || cost < best) {
+            best = cost;
+            h.shape = i;
+            h.tile = tile;
+            h.zero_off = (int)(win - extra);
+            h.lds = (int)((body + 15) / 16 * 16);
+            h.ok = true;
+        }
+    }
+    h.PB = halo_cdiv(P, 16);
+    h.w_elems = (long long)G * h.PB * h.ks * 512;
+    if (h.w_elems * 2 > (1ll << 30)) h.ok = false;
+}
+
 // The convolution as the kernel sees it: the data gradient reads dy and writes the input's shape.
 ConvGeom halo_geom(const ConvGeom& g, bool bwd)
 {
@@ -323,46 +393,28 @@ HaloPlan conv_halo_plan(int dt, const ConvGeom& geom, bool bwd)
         return bwd ? oh + g.PD - (g.K - 1) : oh - g.PD;
     };
     auto clamp = [&](int r) { return std::min(std::max(r, 0), g.H - 1); };
-    double best = 0;
-    for (int i = 0; i < (int)(sizeof kShapes / sizeof kShapes[0]); ++i) {
-        const Shape& s = kShapes[i];
-        const int BP = 16 * s.fp * s.wp, BQ = 16 * s.fq * (s.nw / s.wp);
-        // whole images where they fit and fill the columns, else BQ outputs in a row
-        const int whole = BQ / img * img, tile = whole * 10 >= BQ * 9 ? whole : BQ;
-        // the largest input window of any output tile (tiles repeat their place in an image)
-        int rows = 0;
-        const long long period = (long long)img / std::__gcd(tile, img) * tile;
-        for (long long q0 = 0; q0 < std::min(Q, period); q0 += tile) {
-            const long long q1 = std::min<long long>(q0 + tile, Q) - 1;
-            rows = std::max(rows, (int)((q1 / img - q0 / img) * g.H) + clamp(lo(q1) + g.K - 1) - clamp(lo(q0)) + 1);
-        }
-        const long long win = (long long)rows * g.W * h.stride + h.stride;
-        const long long body = std::max(win, (long long)BQ * (BP + 8) * 2);
-        const long long lds = body + (cg % 64 ? (h.ks + 2) * 32 : 0);
-        if (lds > kCuLds) continue;
-        const long long blocks = (Q + tile - 1) / tile * halo_cdiv(P, BP) * g.G;
-        // (fewer blocks than this leave a quarter of the compute units idle, where the implicit
-        // GEMM's smaller tiles do not)
-        if (blocks < 192) continue;
-        // products per SIMD on the busiest compute unit; the fewer waves a SIMD has, the more of
-        // the fragment reads' latency shows, and one block per unit overlaps no staging
-        const int res = std::min<int>(s.res, (int)(kCuLds / ((lds + kLdsUnit - 1) / kLdsUnit * kLdsUnit)));
-        const long long n = (blocks + 255) / 256;
-        const int waves = (int)std::min<long long>(res, n) * s.nw / 4;
-        const double cost = (double)n * s.nw / 4 * s.fp * s.fq * s.weight *
-                            (waves < 2 ? 1.35 : waves < 3 ? 1.07 : 1.0) * (n == 1 ? 1.05 : 1.0);
-        if (best == 0 || cost < best) {
-            best = cost;
-            h.shape = i;
-            h.tile = tile;
-            h.zero_off = (int)(win - h.stride);
-            h.lds = (int)body;
-            h.ok = true;
-        }
-    }
-    h.PB = halo_cdiv(P, 16);
-    h.w_elems = (long long)g.G * h.PB * h.ks * 512;
-    if (h.w_elems * 2 > (1ll << 30)) h.ok = false;
+    choose_shape(h, Q, img, P, g.G, (long long)g.W * h.stride, h.stride,
+                 cg % 64 ? (h.ks + 2) * 32 : 0, [&](long long q0, long long q1) {
+                     return (q1 / img - q0 / img) * g.H + clamp(lo(q1) + g.K - 1) - clamp(lo(q0)) + 1;
+                 });
+    return h;
+}
+
+HaloPlan conv_halo_run_plan(int dt, const ConvGeom& g, const RunGeom& r)
+{
+    HaloPlan h{};
+    const int img = g.OH * g.OW;
+    const long long Q = (long long)g.N * img;
+    if (dt != DT_BF16 || g.K < 2 || g.G != 1 || Q > (1ll << 30)) return h;
+    if (plan_for(dt, conv_fwd_run_dims(dt, g, r)).splits > 1) return h;
+    h.ckg = r.RUN / 8;
+    h.ks = halo_cdiv(g.K * h.ckg, 8) * 2;
+    choose_shape(h, Q, img, g.OC, 1, (long long)r.Wp * r.Cp * 2, r.RUN * 2 + 16, (h.ks + 2) * 32,
+                 [&](long long q0, long long q1) {
+                     auto row = [&](long long q) { return q / img * r.Hp + q % img / g.OW * g.S; };
+                     return row(q1) + g.K - row(q0);
+                 });
+    h.zero_off += r.RUN * 2;  // behind the run that the last row may read past its end
     return h;
 }
 
@@ -372,33 +424,25 @@ static void launch_halo(HaloArgs& a, const HaloPlan& h, bool bwd, hipStream_t s)
     constexpr int BP = 16 * FP * WP, BQ = 16 * FQ * (NW / WP);
     a.PT = halo_cdiv(a.P, BP);
     const dim3 grid((unsigned)(halo_cdiv(a.Q, a.tile) * a.PT * a.G)), block(64 * NW);
-    const size_t lds = (size_t)h.lds + (a.cg % 64 ? (size_t)(h.ks + 2) * 32 : 0);
+    const size_t lds = (size_t)h.lds + (a.cg % 64 || a.row ? (size_t)(h.ks + 2) * 32 : 0);
     note_gemm(BP / 32, BQ / 32, 32, 1, kGemmHalo);
-    auto go = [&](auto bwd_, auto c64) {
-        hipLaunchKernelGGL((conv_halo_kernel<NW, FP, WP, FQ, decltype(bwd_)::value, decltype(c64)::value>),
+    auto go = [&](auto bwd_, auto mode) {
+        hipLaunchKernelGGL((conv_halo_kernel<NW, FP, WP, FQ, decltype(bwd_)::value, decltype(mode)::value>),
                            grid, block, lds, s, a);
     };
+    typedef std::integral_constant<int, M_ANY> Any;
+    typedef std::integral_constant<int, M_C64> C64;
+    typedef std::integral_constant<int, M_RUN> Run;
     const bool c64 = a.cg % 64 == 0;
-    if (bwd && c64) go(std::true_type{}, std::true_type{});
-    else if (bwd) go(std::true_type{}, std::false_type{});
-    else if (c64) go(std::false_type{}, std::true_type{});
-    else go(std::false_type{}, std::false_type{});
+    if (a.row) go(std::false_type{}, Run{});
+    else if (bwd && c64) go(std::true_type{}, C64{});
+    else if (bwd) go(std::true_type{}, Any{});
+    else if (c64) go(std::false_type{}, C64{});
+    else go(std::false_type{}, Any{});
 }
 
-hipError_t conv_halo(const ConvGeom& geom, const HaloPlan& h, bool bwd, const void* x, const void* w,
-                     const float* bias, bool relu, const void* mask, void* y, hipStream_t s)
+static hipError_t launch_shape(HaloArgs& a, const HaloPlan& h, const ConvGeom& g, bool bwd, hipStream_t s)
 {
-    if (!h.ok) return hipErrorInvalidValue;
-    const ConvGeom g = halo_geom(geom, bwd);
-    HaloArgs a{};
-    a.x = static_cast<const bf16_t*>(x); a.w = static_cast<const bf16_t*>(w);
-    a.bias = bias; a.mask = static_cast<const bf16_t*>(mask); a.y = static_cast<bf16_t*>(y);
-    a.x_bytes = (unsigned)((size_t)g.N * g.C * g.H * g.W * 2);
-    a.w_bytes = (unsigned)(h.w_elems * 2);
-    a.y_bytes = (unsigned)((size_t)g.N * g.OC * g.OH * g.OW * 2);
-    a.N = g.N; a.C = g.C; a.H = g.H; a.W = g.W; a.OC = g.OC; a.OH = g.OH; a.OW = g.OW;
-    a.K = g.K; a.PD = g.PD; a.G = g.G;
-    a.cg = g.C / g.G; a.P = g.OC / g.G; a.Q = g.N * g.OH * g.OW; a.relu = relu;
     a.tile = h.tile; a.ckg = h.ckg; a.ks = h.ks; a.stride = h.stride; a.PB = h.PB;
     a.zero_off = h.zero_off; a.tab_off = h.lds;
     a.vout = a.P % 8 == 0 ? 8 : 1;
@@ -418,6 +462,39 @@ hipError_t conv_halo(const ConvGeom& geom, const HaloPlan& h, bool bwd, const vo
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+hipError_t conv_halo(const ConvGeom& geom, const HaloPlan& h, bool bwd, const void* x, const void* w,
+                     const float* bias, bool relu, const void* mask, void* y, hipStream_t s)
+{
+    if (!h.ok) return hipErrorInvalidValue;
+    const ConvGeom g = halo_geom(geom, bwd);
+    HaloArgs a{};
+    a.x = static_cast<const bf16_t*>(x); a.w = static_cast<const bf16_t*>(w);
+    a.bias = bias; a.mask = static_cast<const bf16_t*>(mask); a.y = static_cast<bf16_t*>(y);
+    a.x_bytes = (unsigned)((size_t)g.N * g.C * g.H * g.W * 2);
+    a.w_bytes = (unsigned)(h.w_elems * 2);
+    a.y_bytes = (unsigned)((size_t)g.N * g.OC * g.OH * g.OW * 2);
+    a.N = g.N; a.C = g.C; a.H = g.H; a.W = g.W; a.OC = g.OC; a.OH = g.OH; a.OW = g.OW;
+    a.K = g.K; a.PD = g.PD; a.G = g.G;
+    a.cg = g.C / g.G; a.P = g.OC / g.G; a.Q = g.N * g.OH * g.OW; a.relu = relu;
+    return launch_shape(a, h, g, bwd, s);
+}
+
+hipError_t conv_halo_run(const ConvGeom& g, const RunGeom& r, const HaloPlan& h, const void* xp,
+                         const void* w, const float* bias, bool relu, void* y, hipStream_t s)
+{
+    if (!h.ok || g.G != 1) return hipErrorInvalidValue;
+    HaloArgs a{};
+    a.x = static_cast<const bf16_t*>(xp); a.w = static_cast<const bf16_t*>(w);
+    a.bias = bias; a.y = static_cast<bf16_t*>(y);
+    a.x_bytes = (unsigned)((size_t)g.N * r.Hp * r.Wp * r.Cp * 2);
+    a.w_bytes = (unsigned)(h.w_elems * 2);
+    a.y_bytes = (unsigned)((size_t)g.N * g.OC * g.OH * g.OW * 2);
+    a.N = g.N; a.C = r.Cp; a.H = g.H; a.W = g.W; a.OC = g.OC; a.OH = g.OH; a.OW = g.OW;
+    a.K = g.K; a.PD = 0; a.G = 1; a.S = g.S; a.Hp = r.Hp; a.row = r.Wp * r.Cp;
+    a.cg = r.Cp; a.P = g.OC; a.Q = g.N * g.OH * g.OW; a.relu = relu;
+    return launch_shape(a, h, g, false, s);
 }
 
 }  // namespace mtx

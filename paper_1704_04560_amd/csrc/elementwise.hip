@@ -175,6 +175,7 @@ void prep_fill_divisors(PrepJob& j)
         break;
     case PREP_HALO_F:
     case PREP_HALO_D:
+    case PREP_HALO_RUN:
         j.f0 = make_fastdiv((unsigned)j.K);
         j.f1 = make_fastdiv((unsigned)j.Cp);
         j.f2 = make_fastdiv((unsigned)j.RUN);

@@ -170,6 +170,7 @@ enum PrepKind {
     PREP_CONV_RUN,   // Wr[co][u][j] of a first-layer convolution over a padded input
     PREP_HALO_F,     // fragment-major weights of conv_halo, forward
     PREP_HALO_D,     // ... data gradient
+    PREP_HALO_RUN,   // ... forward over a padded first-layer input
 };
 struct PrepJob {
     int kind;
@@ -178,7 +179,8 @@ struct PrepJob {
     long long dst;     // element offset in the prepared buffer
     int g, cg, og, KK; // convolution: groups, channels per group in / out, K*K
     int C, HW, IN;     // fully connected permutation; C, Cp, K, RUN of a padded first layer;
-                       // Cp, K, RUN = granules per tap, k steps, row blocks (halo)
+                       // Cp, K, RUN = granules per tap, k steps, row blocks (halo; for a
+                       // padded first layer C, HW, IN = C, Cp, K and a tap is a kernel row)
     int Cp, K, RUN;
     int block0;        // first block of this job in the launch
     FastDiv f0, f1, f2;
@@ -350,5 +352,10 @@ hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const v
                            float* grads, long long ld, long long w_off, float* partial, hipStream_t s);
 hipError_t conv_halo(const ConvGeom& g, const HaloPlan& h, bool bwd, const void* x, const void* w,
                      const float* bias, bool relu, const void* mask, void* y, hipStream_t s);
+
+// The forward of a padded first layer (conv_fwd_run), weights PREP_HALO_RUN.
+HaloPlan conv_halo_run_plan(int dt, const ConvGeom& g, const RunGeom& r);
+hipError_t conv_halo_run(const ConvGeom& g, const RunGeom& r, const HaloPlan& h, const void* xp,
+                         const void* w, const float* bias, bool relu, void* y, hipStream_t s);
 
 }  // namespace mtx

@@ -54,6 +54,15 @@ __device__ __forceinline__ int prep_src(const PrepJob& j, unsigned d)
         const unsigned co = fwd ? p : c, ci = fwd ? c : p;
         return (int)((g * (unsigned)j.og + co) * (unsigned)j.cg + ci) * j.KK + (int)tap;
     }
+    case PREP_HALO_RUN: {  // d = (pb*ks + k)*512 + lane*8 + e; granule (u, c8) of run element c8*8 + e
+        const unsigned e = d & 7u, lane = (d >> 3) & 63u;
+        const unsigned r1 = d >> 9, pb = prep_fdivu(j.f0, r1), k = r1 - pb * (unsigned)j.K;
+        const unsigned gi = k * 4u + (lane >> 4), u = prep_fdivu(j.f1, gi);
+        const unsigned co = pb * 16u + (lane & 15u), jj = (gi - u * (unsigned)j.Cp) * 8u + e;
+        const unsigned v = jj / (unsigned)j.HW, ci = jj - v * (unsigned)j.HW, K = (unsigned)j.IN;
+        if (u >= K || v >= K || ci >= (unsigned)j.C || co >= (unsigned)j.og) return -1;
+        return (int)(((co * (unsigned)j.C + ci) * K + u) * K + v);
+    }
     case PREP_FC_PERM: {  // d = o*IN + hw*C + c
         const unsigned o = prep_fdivu(j.f0, d), r = d - o * (unsigned)j.IN;
         const unsigned hw = prep_fdivu(j.f1, r), c = r - hw * (unsigned)j.C;

@@ -36,6 +36,13 @@ CASES = {
     "image": ((64, 13, 13), (wl.conv(192, 3, pad=1, relu=True), wl.conv(384, 3, pad=1, groups=2),
                              wl.fc(3)), 2, 200,
               {("fwd", 0, 192), ("fwd", 1, 192), ("dgrad", 1, 96)}),
+    # padded first layers: stride 4 with rows past a tile's end, 8-channel pixels, odd channels
+    "first": ((3, 51, 47), (wl.conv(70, 11, stride=4, pad=2, relu=True), wl.maxpool(3, 2), wl.fc(4)),
+              3, 80, {("fwd", 0, None)}),
+    "first3": ((3, 33, 31), (wl.conv(20, 3, pad=1, relu=True), wl.maxpool(3, 2), wl.fc(3)), 2, 60,
+               {("fwd", 0, 32)}),
+    "first5": ((5, 40, 42), (wl.conv(24, 5, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 95,
+               {("fwd", 0, 32)}),
     "wide": ((64, 13, 13), (wl.conv(256, 3, pad=1, relu=True), wl.conv(384, 3, pad=1), wl.fc(3)), 1,
              200, {("fwd", 1, 384), ("dgrad", 1, 256)}),
 }
