@@ -12,6 +12,7 @@
 // stores; the others take one element per thread.
 #include "device_common.h"
 #include "internal.h"
+#include "prep.h"
 
 namespace mtx {
 
@@ -641,6 +642,52 @@ hipError_t add_bwd(Dt dt, size_t n, const void* dy, void* dx, const void* mask, 
                            static_cast<const bf16_t*>(dy), static_cast<bf16_t*>(dx), mask,
                            mask_f32 ? 1 : 0, static_cast<bf16_t*>(skip), smask,
                            smask_f32 ? 1 : 0, total);
+    return hipGetLastError();
+}
+
+// Strided projection: dy at every S-th row and column += its share, masked; one vector per thread.
+// Bound by its reads: the compact share and the positions it meets, a third of the bytes of the
+// full-size share's addition at stride 2 (256 channels of 32 x 32 at batch 256: 40 -> 23 us).
+template <typename T>
+__global__ __launch_bounds__(256) void skip_add_strided_kernel(T* __restrict__ dy, const T* __restrict__ skip,
+                                                               const void* __restrict__ smask, int smask_f32,
+                                                               int H, int W, int C, int S, int OH, int OW,
+                                                               FastDiv fcv, FastDiv fow, FastDiv foh,
+                                                               unsigned nvec)
+{
+    constexpr int V = 16 / sizeof(T);
+    const unsigned t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= nvec) return;
+    const unsigned p = prep_fdivu(fcv, t), c = t - p * (unsigned)(C / V);
+    const unsigned r = prep_fdivu(fow, p), ow = p - r * (unsigned)OW;
+    const unsigned n = prep_fdivu(foh, r), oh = r - n * (unsigned)OH;
+    const size_t e = (((size_t)n * H + oh * S) * W + ow * S) * C + (size_t)c * V;
+    float a[V], b[V], m[V];
+    load_vec<T, V>(dy + e, a);
+    load_vec<T, V>(skip + (size_t)t * V, b);
+    load_mask<T, V>(smask, smask_f32, e, m);
+#pragma unroll
+    for (int k = 0; k < V; ++k) a[k] += m[k] > 0.f ? b[k] : 0.f;
+    store_vec<T, V>(dy + e, a);
+}
+
+hipError_t skip_add_strided(Dt dt, const ConvGeom& g, void* dy, const void* skip, const void* smask,
+                            bool smask_f32, hipStream_t s)
+{
+    const int V = dt == DT_F32 ? 4 : 8;
+    if (g.C % V) return hipErrorInvalidValue;
+    const unsigned nv = (unsigned)((size_t)g.N * g.OH * g.OW * (g.C / V));
+    const dim3 grid((nv + 255) / 256);
+    const FastDiv fcv = make_fastdiv((unsigned)(g.C / V)), fow = make_fastdiv((unsigned)g.OW),
+                  foh = make_fastdiv((unsigned)g.OH);
+    if (dt == DT_F32)
+        hipLaunchKernelGGL((skip_add_strided_kernel<float>), grid, dim3(256), 0, s,
+                           static_cast<float*>(dy), static_cast<const float*>(skip), smask,
+                           smask_f32 ? 1 : 0, g.H, g.W, g.C, g.S, g.OH, g.OW, fcv, fow, foh, nv);
+    else
+        hipLaunchKernelGGL((skip_add_strided_kernel<bf16_t>), grid, dim3(256), 0, s,
+                           static_cast<bf16_t*>(dy), static_cast<const bf16_t*>(skip), smask,
+                           smask_f32 ? 1 : 0, g.H, g.W, g.C, g.S, g.OH, g.OW, fcv, fow, foh, nv);
     return hipGetLastError();
 }
 
