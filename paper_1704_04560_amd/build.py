@@ -16,7 +16,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmtx.so")
 SOURCES = ["api.hip", "plan.hip", "igemm_fwd.hip", "igemm_dgrad.hip", "igemm_wgrad.hip",
            "elementwise.hip", "norm.hip", "firstconv.hip", "dgrad_fused.hip", "conv_halo.hip",
-           "conv_halo_wgrad.hip"]
+           "conv_halo_wgrad.hip", "conv_dgrad_s2.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

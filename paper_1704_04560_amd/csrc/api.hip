@@ -387,6 +387,7 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true
             ConvGeom gs = gb;
             gs.N = pl.Nb;
             if (halo) lp.whalo = conv_halo_wgrad_plan(pl.dt, gs, pl.R);
+            if (halo && lp.need_dx && !lp.bhalo.ok) lp.bhalo = conv_dgrad_s2_plan(pl.dt, gb);
             if (lp.bhalo.ok) {
                 lp.bw_off = halo_job(lp.bhalo, PREP_HALO_D);
             } else if (lp.need_dx) {
@@ -1415,6 +1416,8 @@ static int enqueue_step(mtx_model* m, const float* x, const int32_t* labels, flo
                 ConvGeom g{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
                 float* col = reinterpret_cast<float*>(ws + pl.col_off);
                 HIP_TRY(launch_site(m, "dgrad", l, s, [&] {
+                            if (lp.bhalo.ok && lp.s == 2)
+                                return conv_dgrad_s2(g, lp.bhalo, dy, bwd_w(lp), mask, dx, s);
                             if (lp.bhalo.ok)
                                 return conv_halo(g, lp.bhalo, true, dy, bwd_w(lp), nullptr, false,
                                                  mask, dx, s);

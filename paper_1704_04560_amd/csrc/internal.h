@@ -357,6 +357,11 @@ hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const v
 hipError_t conv_halo(const ConvGeom& g, const HaloPlan& h, bool bwd, const void* x, const void* w,
                      const float* bias, bool relu, const void* mask, void* y, hipStream_t s);
 
+// conv_dgrad_s2.hip: bf16 data gradient at stride 2 over windows of dy, weights PREP_HALO_D; the
+// same bits as conv_dgrad_col.
+HaloPlan conv_dgrad_s2_plan(int dt, const ConvGeom& g);
+hipError_t conv_dgrad_s2(const ConvGeom& g, const HaloPlan& h, const void* dy, const void* w,
+                         const void* mask, void* dx, hipStream_t s);
 // The forward of a padded first layer (conv_fwd_run), weights PREP_HALO_RUN.
 HaloPlan conv_halo_run_plan(int dt, const ConvGeom& g, const RunGeom& r);
 hipError_t conv_halo_run(const ConvGeom& g, const RunGeom& r, const HaloPlan& h, const void* xp,

@@ -1,7 +1,8 @@
 """GPU parity of the convolutions that hold their input windows in LDS (bf16) against the oracle,
 and against the implicit GEMM bit for bit: block shapes, channel counts that are not multiples of
 32 or 64, output channels off every vector width, ragged reduction steps, unpadded and grouped
-layers, tiles that cross images, whole-image tiles."""
+layers, tiles that cross images, whole-image tiles, padded first layers, data gradients at stride 2;
+and of the weight gradients over windows."""
 import numpy as np
 import pytest
 import torch
@@ -36,6 +37,19 @@ CASES = {
     "image": ((64, 13, 13), (wl.conv(192, 3, pad=1, relu=True), wl.conv(384, 3, pad=1, groups=2),
                              wl.fc(3)), 2, 200,
               {("fwd", 0, 192), ("fwd", 1, 192), ("dgrad", 1, 96)}),
+    # data gradients at stride 2: odd sizes, scalar stores, 2x2, 5x5 and 7x7 kernels, groups, both
+    # block shapes
+    "stride2": ((3, 33, 30), (wl.conv(24, 3, pad=1, relu=True), wl.conv(64, 3, stride=2, pad=1, relu=True),
+                              wl.maxpool(2, 2), wl.fc(3)), 2, 30, {("dgrad", 1, 64)}),
+    "stride2g": ((3, 33, 30), (wl.conv(64, 3, pad=1, relu=True),
+                               wl.conv(128, 3, stride=2, pad=1, groups=2, relu=True),
+                               wl.maxpool(2, 2), wl.fc(3)), 2, 48, {("dgrad", 1, 64)}),
+    "stride2k2": ((3, 14, 18), (wl.conv(20, 3, pad=1, relu=True), wl.conv(64, 2, stride=2, relu=True),
+                                wl.fc(3)), 2, 120, {("dgrad", 1, 64)}),
+    "stride2k5": ((3, 27, 24), (wl.conv(72, 3, pad=1), wl.conv(64, 5, stride=2, pad=2, relu=True),
+                                wl.maxpool(2, 2), wl.fc(3)), 2, 40, {("dgrad", 1, 128)}),
+    "stride2k7": ((3, 21, 23), (wl.conv(12, 3, pad=1, relu=True), wl.conv(64, 7, stride=2, pad=3, relu=True),
+                                wl.maxpool(2, 2), wl.fc(3)), 2, 70, {("dgrad", 1, 64)}),
     # padded first layers: stride 4 with rows past a tile's end, 8-channel pixels, odd channels
     "first": ((3, 51, 47), (wl.conv(70, 11, stride=4, pad=2, relu=True), wl.maxpool(3, 2), wl.fc(4)),
               3, 80, {("fwd", 0, None)}),
