@@ -1,4 +1,4 @@
-// Convolution forward and data gradient (bf16, stride 1, K x K kernels from 2 x 2 to 7 x 7) over
+// Convolution forward and data gradient (bf16, stride 1, K x K kernels up to 7 x 7) over
 // an input window held in LDS.
 //
 // The implicit GEMM (igemm.h) stages every k tile of its activation operand through LDS, so an
@@ -377,7 +377,7 @@ ConvGeom halo_geom(const ConvGeom& g, bool bwd)
 HaloPlan conv_halo_plan(int dt, const ConvGeom& geom, bool bwd)
 {
     HaloPlan h{};
-    if (dt != DT_BF16 || geom.K < 2 || geom.K > 7 || geom.S != 1) return h;
+    if (dt != DT_BF16 || geom.K > 7 || geom.S != 1) return h;
     const ConvGeom g = halo_geom(geom, bwd);
     const int cg = g.C / g.G, P = g.OC / g.G, img = g.OH * g.OW;
     const long long Q = (long long)g.N * img;
@@ -397,6 +397,11 @@ HaloPlan conv_halo_plan(int dt, const ConvGeom& geom, bool bwd)
                  cg % 64 ? (h.ks + 2) * 32 : 0, [&](long long q0, long long q1) {
                      return (q1 / img - q0 / img) * g.H + clamp(lo(q1) + g.K - 1) - clamp(lo(q0)) + 1;
                  });
+    // A 1 x 1 kernel reads its input once either way.  The implicit GEMM's masked output is its slow
+    // part: data gradient of 256 -> 128 channels, 32 x 32, batch 256: 124 -> 68 us here (a copy of
+    // its bytes: 66).  Not where a window leaves room for one block per unit (512 -> 128, 16 x 16: 22
+    // us against 29 here), and not forward (256 -> 128 51 against 61, 128 -> 512 29 against 31).
+    if (geom.K == 1 && (!bwd || h.lds > kHaloMaxLds)) h.ok = false;
     return h;
 }
 

@@ -37,6 +37,10 @@ CASES = {
     "image": ((64, 13, 13), (wl.conv(192, 3, pad=1, relu=True), wl.conv(384, 3, pad=1, groups=2),
                              wl.fc(3)), 2, 200,
               {("fwd", 0, 192), ("fwd", 1, 192), ("dgrad", 1, 96)}),
+    # 1x1 data gradients: scalar stores off the fragments, groups
+    "pointwise": ((3, 33, 31), (wl.conv(20, 3, pad=1, relu=True), wl.conv(72, 1, relu=True),
+                                wl.conv(48, 1, groups=3, relu=True), wl.maxpool(3, 2), wl.fc(3)), 2, 32,
+                  {("dgrad", 1, 32), ("dgrad", 2, 32)}),
     # data gradients at stride 2: odd sizes, scalar stores, 2x2, 5x5 and 7x7 kernels, groups, both
     # block shapes
     "stride2": ((3, 33, 30), (wl.conv(24, 3, pad=1, relu=True), wl.conv(64, 3, stride=2, pad=1, relu=True),
