@@ -371,16 +371,17 @@ __global__ __launch_bounds__(256) void halo_wgrad_reduce(const float* __restrict
 
 // ---- plan -------------------------------------------------------------------------------------
 namespace {
-// Reduction splits of a planned launch: as few as give every compute unit a block, of at least two
-// tiles: the partial rows that a second block per unit would write and read back cost more than it
-// gains (two per unit: CIFAR step 828 -> 863 us, residual block 558 -> 580, AlexNet 2370 -> 2427),
-// and the data-gradient chain on the other stream runs beside one.
+// Reduction splits of a planned launch: as few as give every compute unit a block, of at least three
+// tiles (with two, 88 channels of a small layer took 16 to 18 us against the implicit GEMM's 14.6):
+// the partial rows that a second block per unit would write and read back cost more than it gains
+// (two per unit: CIFAR step 828 -> 863 us, residual block 558 -> 580, AlexNet 2370 -> 2427), and the
+// data-gradient chain on the other stream runs beside one.
 void choose_splits(HaloWPlan& h, int R, int G)
 {
     const long long base = (long long)R * G * h.cot * h.ubs;
     h.ld = (h.n + 3) / 4 * 4;
     long long splits = (256 + base - 1) / base;
-    splits = std::min<long long>(splits, std::max(1, h.tiles / 2));
+    splits = std::min<long long>(splits, std::max(1, h.tiles / 3));
     while (splits > 1 && splits * R * h.ld > (64ll << 20)) --splits;
     h.tps = halo_cdiv(h.tiles, (int)splits);
     h.splits = halo_cdiv(h.tiles, h.tps);
@@ -393,6 +394,10 @@ HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R)
     HaloWPlan h{};
     const int cg = g.C / g.G, og = g.OC / g.G;
     if (dt != DT_BF16 || (g.K != 2 && g.K != 3 && g.K != 5 && g.K != 7) || g.S > 2 || cg < 8) return h;
+    // (element-wise loads only for grouped layers, whose operand rows are short in the implicit GEMM
+    // too: a step with 2 groups of 10 -> 18 channels 585 -> 564 us; ungrouped, 19 -> 13 channels took
+    // 38 us against the implicit GEMM's 33, and 225 -> 153 43 against 34)
+    if (g.G == 1 && (cg % 4 || og % 4)) return h;
     const long long Q = (long long)g.N * g.OH * g.OW;
     if (Q > (1ll << 30)) return h;
     h.Hp = (g.OH - 1) * g.S + g.K;
