@@ -86,7 +86,8 @@ __global__ __launch_bounds__(512, 4) void conv_dgrad_s2_kernel(const HaloS2Args 
             if (t < ngran) *reinterpret_cast<u32x4*>(lds + pos * a.stride + g * 16) = v[s];
         }
     }
-    if (tid < ckg) *reinterpret_cast<u32x4*>(lds + a.zero_off + tid * 16) = u32x4{0u, 0u, 0u, 0u};
+    for (int i = tid; i < ckg; i += NT)
+        *reinterpret_cast<u32x4*>(lds + a.zero_off + i * 16) = u32x4{0u, 0u, 0u, 0u};
 
     int base[FQ], ok[FQ];  // origin (tap u0, v0), valid taps t (bits 0.. rows, 8.. columns)
 #pragma unroll

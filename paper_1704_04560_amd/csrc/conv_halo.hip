@@ -117,8 +117,10 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
         for (int s = 0; s < NS; ++s)
             if (t0 + s * NT < ngran) *reinterpret_cast<u32x4*>(lds + dst[s]) = v[s];
     }
-    // the zero position that taps in the padding read
-    if (tid < (RUN ? 1 : a.ckg)) *reinterpret_cast<u32x4*>(lds + a.zero_off + tid * 16) = u32x4{0u, 0u, 0u, 0u};
+    // the zero position that taps in the padding read (it may have more granules than the block has
+    // threads)
+    for (int i = tid; i < (RUN ? 1 : a.ckg); i += NT)
+        *reinterpret_cast<u32x4*>(lds + a.zero_off + i * 16) = u32x4{0u, 0u, 0u, 0u};
     // table of the reduction granules i = (u, v, c8) in ascending order: LDS byte offset from an
     // output's origin, and the two validity bits the tap needs
     const int ngr = (RUN ? a.K : a.K * a.K) * a.ckg;

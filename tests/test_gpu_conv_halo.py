@@ -138,3 +138,42 @@ def test_window_weight_gradients_match_oracle(name):
     model.close()
     assert expected <= set(seen), (expected, seen)
     run_case("halo-wgrad-" + name, net, R, Nb, 1, 3, 0.01, 0.9)
+
+
+def test_padding_reads_zeros_in_every_channel():
+    """1 x 1 images of 2112 channels under a 2 x 2 kernel with three positions of padding, on the
+    four-wave block: 264 granules per position, more than the block has threads.  Four of 36
+    outputs have a tap inside the image; all others are the bias."""
+    B, C, OC = 1024, 2112, 192
+    net = wl.Net("halo-zero", (C, 1, 1), (wl.conv(OC, 2, pad=3), wl.fc(3)), wl.BF16, "normal")
+    model = mtx.Model(net.in_shape, wl.layer_tuples(net), wl.BF16, 2, B // 2, seed=1)
+    rng = np.random.default_rng(3)
+    w, _ = model.get_params()
+    bias = rng.standard_normal(OC).astype(np.float32)
+    w[C * OC * 4:C * OC * 4 + OC] = bias
+    model.set_params(w)
+    x, y = wl.make_batch(net, B, seed=3)
+    model.train_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.0, 0.0)
+    tiles = [(l["tile_rows"], l["tile_cols"]) for l in mtx.mtx_get_launches(model.handle)
+             if l["flags"] & mtx.MTX_GEMM_HALO and l["site"] == "fwd"]
+    out = model.layer_output(0).reshape(B, OC, 6, 6)
+    model.close()
+    assert tiles == [(192, 160)]
+
+    def bf16(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).bfloat16().double()
+
+    expected = bf16(bias).view(1, OC, 1, 1).repeat(B, 1, 6, 6)
+    taps = bf16(w[:C * OC * 4].reshape(OC, C, 2, 2))
+    for u in range(2):
+        for v in range(2):
+            expected[:, :, 3 - u, 3 - v] = (bf16(x.reshape(B, C)) @ taps[:, :, u, v].t()
+                                            + torch.from_numpy(bias).double())
+    got = torch.from_numpy(out).double()
+    inside = np.zeros((6, 6), bool)
+    inside[2:4, 2:4] = True
+    assert bool((got[:, :, ~inside] == expected[:, :, ~inside]).all())
+    # a rounding to bf16 (2^-9) of a sum of 2112 products in 32 bits (2112 roundings of 2^-24 of
+    # magnitudes that add up to less than 100)
+    error = (got - expected).abs()[:, :, inside]
+    assert (error <= expected.abs()[:, :, inside] * 2.0 ** -8 + 2112 * 100 * 2.0 ** -24).all()
