@@ -183,7 +183,9 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
 #pragma unroll
             for (int i = 0; i < FP; ++i)
                 Mma<bf16_t>::run(acc[i][j], __builtin_bit_cast(s16x8, fa[i]), fb[j]);
-        wload(fa, k + 2);  // (past the last step: the next rows' weights, or zero; not used)
+        // (at the end the last step's again, not used: the buffer's bound covers the per-lane offset
+        // only, so the scalar one must stay inside the weights)
+        wload(fa, min(k + 2, a.ks - 1));
     };
     // two register sets of weight fragments: a set's next fragments are loaded as soon as its
     // products are issued, one k step ahead of their use (an even number of k steps)
