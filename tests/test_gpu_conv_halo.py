@@ -114,10 +114,10 @@ WGRAD_CASES = {
     # a first layer of 8 channels with a 7x7 kernel, stride 2, an unpadded 5x5 layer
     "strided": ((8, 24, 24), (wl.conv(16, 7, pad=3, relu=True), wl.conv(136, 3, stride=2, pad=1, relu=True),
                               wl.conv(64, 5, relu=True), wl.maxpool(2, 2), wl.fc(5)), 32, 5, {0, 1, 2}),
-    # padded first layers: 32- and 64-channel output tiles, two groups and one per window row
-    "first32": ((3, 33, 31), (wl.conv(20, 3, pad=1, relu=True), wl.maxpool(3, 2), wl.fc(3)), 4, 40, {0}),
-    "first64": ((5, 41, 43), (wl.conv(76, 3, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 95, {0}),
-    "first2": ((3, 40, 42), (wl.conv(36, 2, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 120, {0}),
+    # padded first layers (implicit GEMM)
+    "first32": ((3, 33, 31), (wl.conv(20, 3, pad=1, relu=True), wl.maxpool(3, 2), wl.fc(3)), 4, 40, set()),
+    "first64": ((5, 41, 43), (wl.conv(76, 3, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 95, set()),
+    "first2": ((3, 40, 42), (wl.conv(36, 2, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 120, set()),
     # one split: the rows are written straight into gradient rows that start off 16 bytes
     "direct": ((3, 8, 8), (wl.bn(), wl.conv(128, 3, pad=1, relu=True), wl.conv(256, 3, pad=1), wl.fc(3)),
                64, 2, {2}),
