@@ -200,8 +200,7 @@ __global__ __launch_bounds__(512, 4) void conv_dgrad_s2_kernel(const HaloS2Args 
     for (int t = 0; t < NO; ++t) {
         const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
         idx[t] = q0 + q <= q1 && g * 8 < pn ? out_at(q0 + q) + g * 8 : -1;
-        if (a.mask && a.vout == 8)
-            mk[t] = __builtin_amdgcn_raw_buffer_load_b128(bm, idx[t] >= 0 ? idx[t] * 2 : (int)kOOB, 0, 0);
+        if (a.mask && a.vout > 1) mk[t] = halo_row_load(bm, a.vout, idx[t] >= 0, idx[t], pn - g * 8);
     }
     __syncthreads();
 #pragma unroll
@@ -209,15 +208,9 @@ __global__ __launch_bounds__(512, 4) void conv_dgrad_s2_kernel(const HaloS2Args 
         if (idx[t] < 0) continue;
         const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
         u32x4 v = *reinterpret_cast<const u32x4*>(ot + q * OSTR + g * 8);
-        if (a.vout == 8) {
-            if (a.mask)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const unsigned lo = __uint_as_float(mk[t][e] << 16) > 0.f ? 0xffffu : 0u;
-                    const unsigned hi = __uint_as_float(mk[t][e] & 0xffff0000u) > 0.f ? 0xffff0000u : 0u;
-                    v[e] &= lo | hi;
-                }
-            *reinterpret_cast<u32x4*>(a.dx + idx[t]) = v;
+        if (a.vout > 1) {
+            if (a.mask) v = halo_masked(v, mk[t]);
+            halo_row_store(a.dx + idx[t], a.vout, v, pn - g * 8);
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -291,7 +284,7 @@ hipError_t conv_dgrad_s2(const ConvGeom& g, const HaloPlan& h, const void* dy, c
     a.N = g.N; a.C = g.C; a.H = g.H; a.W = g.W; a.OC = g.OC; a.OH = g.OH; a.OW = g.OW;
     a.K = g.K; a.PD = g.PD; a.G = g.G; a.cg = g.C / g.G; a.og = g.OC / g.G;
     a.ks = h.ks; a.stride = h.stride; a.PB = h.PB; a.zero_off = h.zero_off;
-    a.vout = a.cg % 8 == 0 ? 8 : 1;
+    a.vout = halo_row_width(a.cg);
     const int BP = h.shape ? 128 : 64, BQ = h.shape ? 128 : 256;
     int tiles = 0;
     for (int cls = 0; cls < 4; ++cls) {

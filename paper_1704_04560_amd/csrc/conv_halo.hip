@@ -240,19 +240,19 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
     }
 
     // Epilogue: bias and ReLU in fp32, the tile rounded into LDS as [q][p], then whole rows of
-    // channels with 16-byte stores; the data gradient's mask is read with them.
+    // channels with 16-byte stores (8-byte ones where the channels are a multiple of 4 only); the
+    // data gradient's mask is read with them.
     constexpr int OSTR = BP + 8, GP = BP / 8, NO = (BQ * GP + NT - 1) / NT;
     const int pn = min(BP, a.P - p0);
     u32x4 mk[BWD ? NO : 1];
     if constexpr (BWD) {
         // the mask's latency passes while the tile goes to LDS
-        if (a.mask && a.vout == 8) {
+        if (a.mask && a.vout > 1) {
 #pragma unroll
             for (int t = 0; t < NO; ++t) {
                 const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
                 const int idx = (q0 + q) * a.OC + grp * a.P + p0 + g * 8;
-                mk[t] = __builtin_amdgcn_raw_buffer_load_b128(
-                    bm, q0 + q <= q1 && g * 8 < pn ? idx * 2 : (int)kOOB, 0, 0);
+                mk[t] = halo_row_load(bm, a.vout, q0 + q <= q1, idx, pn - g * 8);
             }
         }
     }
@@ -288,17 +288,9 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
         if (q0 + q > q1 || q >= a.tile || g * 8 >= pn) continue;
         u32x4 v = *reinterpret_cast<const u32x4*>(ot + q * OSTR + g * 8);
         const long long idx = (long long)(q0 + q) * a.OC + grp * a.P + p0 + g * 8;
-        if (a.vout == 8) {
-            if (BWD && a.mask) {
-                const u32x4 m = mk[t];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const unsigned lo = __uint_as_float(m[e] << 16) > 0.f ? 0xffffu : 0u;
-                    const unsigned hi = __uint_as_float(m[e] & 0xffff0000u) > 0.f ? 0xffff0000u : 0u;
-                    v[e] &= lo | hi;
-                }
-            }
-            *reinterpret_cast<u32x4*>(a.y + idx) = v;
+        if (a.vout > 1) {
+            if (BWD && a.mask) v = halo_masked(v, mk[t]);
+            halo_row_store(a.y + idx, a.vout, v, pn - g * 8);
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -457,7 +449,7 @@ static hipError_t launch_shape(HaloArgs& a, const HaloPlan& h, const ConvGeom& g
 {
     a.tile = h.tile; a.ckg = h.ckg; a.ks = h.ks; a.stride = h.stride; a.PB = h.PB;
     a.zero_off = h.zero_off; a.tab_off = h.lds;
-    a.vout = a.P % 8 == 0 ? 8 : 1;
+    a.vout = halo_row_width(a.P);
     a.fd_ohw = make_fastdiv((unsigned)(g.OH * g.OW));
     a.fd_ow = make_fastdiv((unsigned)g.OW);
     a.fd_ckg = make_fastdiv((unsigned)h.ckg);
