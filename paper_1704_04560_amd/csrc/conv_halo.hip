@@ -364,6 +364,28 @@ void choose_shape(HaloPlan& h, long long Q, int img, int P, int G, long long row
     if (h.w_elems * 2 > (1ll << 30)) h.ok = false;
 }
 
+// Estimated time of a launch in microseconds (see gemm_us): for every block on the busiest compute unit
+// its products, its window's 16-byte pieces per thread, which cost three times as much where the
+// window leaves room for one block, and its output rows.
+double halo_us(const HaloPlan& h, long long Q, int P, int G)
+{
+    const Shape& s = kShapes[h.shape];
+    const int BP = 16 * s.fp * s.wp;
+    const long long blocks = (Q + h.tile - 1) / h.tile * halo_cdiv(P, BP) * G;
+    const bool alone = s.res == 1 || halo_cdiv(h.lds, kLdsUnit) * kLdsUnit * 2 > kCuLds;
+    const double pieces = h.zero_off / 16.0 / (64 * s.nw), kb = h.tile * std::min(BP, P) * 2e-3;
+    return 6.8 + (double)((blocks + 255) / 256) *
+                     (h.ks * (0.05 + s.fp * s.fq * s.nw / 4 * (alone ? 0.011 : 0.0085)) +
+                      pieces * (alone ? 0.235 : 0.07) + 0.72 + kb * (P % 4 ? 0.196 : 0.049));
+}
+
+// The same of an implicit GEMM that writes bf16 rows (bwd: and reads their mask).
+double direct_us(int dt, const GemmDims& d, bool bwd)
+{
+    return gemm_us(d, plan_for(dt, d), 7.8, kGemmProduct, kGemmOperand) +
+           2.0 * d.P * d.Q * d.Z * (bwd ? 4.4e-7 : 2.1e-7) * (d.P % 4 ? 3.5 : 1.0);
+}
+
 // The convolution as the kernel sees it: the data gradient reads dy and writes the input's shape.
 ConvGeom halo_geom(const ConvGeom& g, bool bwd)
 {
@@ -401,6 +423,16 @@ HaloPlan conv_halo_plan(int dt, const ConvGeom& geom, bool bwd)
     // its bytes: 66).  Not where a window leaves room for one block per unit (512 -> 128, 16 x 16: 22
     // us against 29 here), and not forward (256 -> 128 51 against 61, 128 -> 512 29 against 31).
     if (geom.K == 1 && (!bwd || h.lds > kHaloMaxLds)) h.ok = false;
+    // Small blocks, padded rows and wide windows leave the implicit GEMM ahead: of 651 drawn layers the
+    // kernel was slower in 76 forward and 7 data gradients, with this rule in 28 and 4 (most by a
+    // few percent; 22.42 -> 22.27 ms in sum, the implicit GEMM 26.51).  An unpadded layer's data gradient
+    // multiplies the padding around dy, which the col product does not: the kernel gains up to
+    // about four products for a useful one (256 -> 256 channels, 8 x 8, 5 x 5: 55 us, col 61), for
+    // narrow layers more, and loses beyond (7 x 7 closing 7 x 7 images, 256 -> 256: 133 us, col 38).
+    const GemmDims d = bwd ? conv_dgrad_dims(dt, geom) : conv_fwd_dims(dt, geom);
+    const double other = bwd && conv_dgrad_use_col(geom) ? conv_dgrad_col_us(dt, geom)
+                                                         : 1.1 * direct_us(dt, d, bwd);
+    if (h.ok && halo_us(h, Q, P, g.G) > other) h.ok = false;
     return h;
 }
 
@@ -419,6 +451,7 @@ HaloPlan conv_halo_run_plan(int dt, const ConvGeom& g, const RunGeom& r)
                      return row(q1) + g.K - row(q0);
                  });
     h.zero_off += r.RUN * 2;  // behind the run that the last row may read past its end
+    if (h.ok && halo_us(h, Q, g.OC, 1) > 1.1 * direct_us(dt, conv_fwd_run_dims(dt, g, r), false)) h.ok = false;
     return h;
 }
 

@@ -86,6 +86,13 @@ struct GemmPlan {
     int FP, FQ, BK, splits, kchunk;
 };
 GemmPlan plan_for(int dt, const GemmDims& d);
+// Estimated time of a planned bf16 launch in microseconds: a start, and for every k step of 32 of the
+// blocks on a compute unit its products (FP * FQ) and operand fragments (FP + FQ).  Layers that
+// also have a kernel over LDS windows are decided by such estimates of both.  Their
+// coefficients, here and beside those kernels, are fitted to single launches of 1500 drawn layers of
+// 8 to 1024 channels, 4 x 4 to 128 x 128 images and 1 to 80 GFLOP (standard deviations 10 to 20%).
+double gemm_us(const GemmDims& d, const GemmPlan& g, double start, double product, double operand);
+constexpr double kGemmProduct = 0.0135, kGemmOperand = 0.016;
 size_t partial_elems(int dt, const GemmDims& d);  // fp32 partial sums a launch needs (0 if none)
 GemmDims conv_fwd_dims(int dt, const ConvGeom& g);
 GemmDims conv_dgrad_dims(int dt, const ConvGeom& g);
@@ -93,6 +100,7 @@ GemmDims conv_wgrad_dims(int dt, const ConvGeom& g, int R);
 GemmDims conv_dgrad_col_dims(int dt, const ConvGeom& g);
 size_t conv_dgrad_col_elems(const ConvGeom& g);
 bool conv_dgrad_use_col(const ConvGeom& g);  // data gradient through col + col2im
+double conv_dgrad_col_us(int dt, const ConvGeom& g);  // ... its estimated time (see gemm_us)
 GemmDims fc_fwd_dims(int dt, int B, int IN, int OUT);
 GemmDims fc_dgrad_dims(int dt, int B, int IN, int OUT);
 GemmDims fc_wgrad_dims(int dt, int Nb, int R, int IN, int OUT);

@@ -84,6 +84,13 @@ GemmPlan plan_for(int dt, const GemmDims& d)
     return g;
 }
 
+double gemm_us(const GemmDims& d, const GemmPlan& g, double start, double product, double operand)
+{
+    const double blocks = (double)cdiv(d.P, 32 * g.FP) * cdiv(d.Q, 32 * g.FQ) * d.Z * g.splits;
+    const double steps = std::max(1.0, blocks / 256) * (double)cdiv(cdiv(d.K, g.splits), 32);
+    return start + steps * (product * g.FP * g.FQ + operand * (g.FP + g.FQ));
+}
+
 size_t partial_elems(int dt, const GemmDims& d)
 {
     const GemmPlan g = plan_for(dt, d);
@@ -123,6 +130,13 @@ bool conv_dgrad_use_col(const ConvGeom& g)
     // 875 us implicit)
     const double waste = (double)g.H * g.W / ((double)g.OH * g.OW * g.S * g.S);
     return (waste >= 1.5 || g.S > 1) && conv_dgrad_col_elems(g) * 4 <= (size_t)512 << 20;
+}
+double conv_dgrad_col_us(int dt, const ConvGeom& g)
+{
+    const GemmDims d = conv_dgrad_col_dims(dt, g);
+    const double bytes = 4.0 * (double)conv_dgrad_col_elems(g);
+    return gemm_us(d, plan_for(dt, d), 15, kGemmProduct, kGemmOperand) +
+           bytes * (g.C / g.G % 4 ? 8.2e-7 : 3.3e-7);
 }
 GemmDims conv_fwd_run_dims(int dt, const ConvGeom& g, const RunGeom& r)
 {

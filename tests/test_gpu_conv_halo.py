@@ -140,6 +140,29 @@ def test_window_weight_gradients_match_oracle(name):
     run_case("halo-wgrad-" + name, net, R, Nb, 1, 3, 0.01, 0.9)
 
 
+# name: input shape, layers, shards, shard batch, the launches (site, layer) that stay off the windows
+OTHERWISE = {
+    # a layer that closes its images to 1 x 1: 49 taps of its data gradient for one inside dy
+    "closing": ((3, 7, 7), (wl.conv(128, 3, pad=1, relu=True), wl.conv(128, 7, relu=True), wl.fc(3)),
+                4, 256, {("dgrad", 1)}),
+}
+
+
+@pytest.mark.parametrize("name", sorted(OTHERWISE))
+def test_layers_with_little_to_gain_stay_on_the_general_kernels(name):
+    shape, layers, R, Nb, expected = OTHERWISE[name]
+    net = wl.Net("halo-not-" + name, shape, layers, wl.BF16, "normal")
+    model = mtx.Model(shape, wl.layer_tuples(net), wl.BF16, R, Nb, seed=1)
+    x, y = wl.make_batch(net, R * Nb, seed=1)
+    model.train_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.01, 0.9)
+    torch.cuda.synchronize()
+    seen = {(l["site"], l["layer"]) for l in mtx.mtx_get_launches(model.handle)
+            if l["flags"] & mtx.MTX_GEMM_HALO}
+    model.close()
+    assert not expected & seen, (expected, seen)
+    run_case("halo-not-" + name, net, R, Nb, 1, 3, 0.01, 0.9)
+
+
 def test_padding_reads_zeros_in_every_channel():
     """1 x 1 images of 2112 channels under a 2 x 2 kernel with three positions of padding, on the
     four-wave block: 264 granules per position, more than the block has threads.  Four of 36
