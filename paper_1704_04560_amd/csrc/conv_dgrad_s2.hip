@@ -246,12 +246,14 @@ HaloPlan conv_dgrad_s2_plan(int dt, const ConvGeom& g)
     h.shape = cg <= 64 ? 0 : 1;
     const int BP = h.shape ? 128 : 64, BQ = h.shape ? 128 : 256;
     auto clamp = [&](int r) { return std::min(std::max(r, 0), g.OH - 1); };
-    long long rows = 0, blocks = 0;
+    long long rows = 0, blocks = 0, taps = 0;  // (taps: of all blocks)
     for (int cls = 0; cls < 4; ++cls) {
         const ClassGeom c = class_of(g, cls);
         const long long img = (long long)c.ch * c.cw, Q = img * g.N;
         if (Q > (1ll << 30)) return h;
+        const int v0 = ((cls & 1) + g.PD) & 1, TV = (g.K - v0 + 1) / 2;
         blocks += (Q + BQ - 1) / BQ;
+        taps += (Q + BQ - 1) / BQ * c.TU * TV;
         const long long period = img / std::__gcd<long long>(BQ, img) * BQ;
         for (long long q0 = 0; q0 < std::min(Q, period); q0 += BQ) {
             const long long q1 = std::min(q0 + BQ, Q) - 1;
@@ -267,7 +269,14 @@ HaloPlan conv_dgrad_s2_plan(int dt, const ConvGeom& g)
     h.lds = (int)body;
     h.PB = halo_cdiv(cg, 16);
     h.w_elems = (long long)g.G * h.PB * h.ks * 512;
-    h.ok = h.w_elems * 2 <= (1ll << 30);
+    // Estimated time (see gemm_us): products and window pieces of the blocks on a compute unit.  Few
+    // input channels fill a block's 64 rows badly: 8 <- 192 channels, 22 x 22, 3 x 3, 1920 images took
+    // 169 us here, the col product 71 (23 drawn layers: 3 were slower, with this rule 1, by 5%).
+    const double per_cu = halo_cdiv(cg, BP) * g.G / 256.0;
+    const double us = 10.3 + per_cu * ((double)taps * (og / 32) * 16 * 0.014 +
+                                       (double)blocks * (2.4 + h.zero_off / 16.0 / 512 *
+                                                                   (h.lds > kHaloMaxLds ? 0.39 : 0.19)));
+    h.ok = h.w_elems * 2 <= (1ll << 30) && us <= conv_dgrad_col_us(dt, g);
     return h;
 }
 

@@ -145,6 +145,9 @@ OTHERWISE = {
     # a layer that closes its images to 1 x 1: 49 taps of its data gradient for one inside dy
     "closing": ((3, 7, 7), (wl.conv(128, 3, pad=1, relu=True), wl.conv(128, 7, relu=True), wl.fc(3)),
                 4, 256, {("dgrad", 1)}),
+    # 8 input channels in 64-row blocks at stride 2
+    "stride2c8": ((3, 22, 22), (wl.conv(8, 3, pad=1, relu=True), wl.conv(192, 3, stride=2, pad=1, relu=True),
+                                wl.maxpool(2, 2), wl.fc(3)), 8, 40, {("dgrad", 1)}),
 }
 
 
