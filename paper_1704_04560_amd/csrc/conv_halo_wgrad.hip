@@ -20,6 +20,7 @@
 // 512 114 -> 71 us; 16 x 16, 128 -> 128 75 -> 67 us; 2 groups of 20 -> 36 channels (narrow loads)
 // 86 -> 55 us.
 #include <algorithm>
+#include <cmath>
 
 #include "halo.h"
 
@@ -385,6 +386,27 @@ HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R)
     h.tps = halo_cdiv(h.tiles, (int)splits);
     h.splits = halo_cdiv(h.tiles, h.tps);
     if (base * h.splits < 192) h.ok = false;
+    // Estimated time of both (see gemm_us).  Here, per tile of the busiest compute unit: its products or
+    // the latency of its loads, the fragment reads, window granules past the prefetched ones, narrow
+    // loads; then the splits' rows.  The implicit GEMM pays for narrow loads too, and for its scattered
+    // gradient stores.  Channel counts that fill the 64 x 16 fragments badly, wide windows (64 -> 32
+    // channels, 52 x 52, unpadded: 201 us against 148) and few products per tile (416 -> 4 channels: 296
+    // against 173) are left to it: of 720 drawn layers 239 were slower here, with this rule 29 (49.1
+    // -> 48.8 ms in sum; 55.6 all on the implicit GEMM, 51.2 without the rule).
+    const int accs = g.K * h.ng * h.fa, odd = cg % 4 || og % 4 ? 2 : cg % 8 || og % 8 ? 1 : 0;
+    const double n = (double)((base * h.splits + 255) / 256), gran = (double)h.xlds / h.stride * h.ckg / 256;
+    const double tile = std::max(0.0417 * accs * n, 1.86 * std::ceil(n / 2)) +
+                        n * (0.048 * (g.K * h.ng + h.fa) + 0.106 * std::max(0.0, gran - halo_w_nx(accs)) +
+                             (odd == 2 ? 0.124 : odd ? 0.0165 : 0.0) * (gran + h.fa));
+    const double us = 14 + h.tps * tile + 2.8e-7 * R * h.ld * (h.splits > 1 ? h.splits * 8 : 4);
+    const GemmDims d = conv_wgrad_dims(dt, g, R);
+    const GemmPlan p = plan_for(dt, d);
+    const double narrow = gemm_us(d, p, 0, 0, 1) / (p.FP + p.FQ) *  // (k steps)
+                          (0.072 * p.FQ * (cg % 8 > 0) + 0.034 * p.FP * (og % 8 > 0));
+    const double out = 4.0 * d.P * d.Q * d.Z;
+    const double other = gemm_us(d, p, 17.5, 0.0114, 0.0255) + narrow +
+                         out * (6.9e-7 + (p.splits > 1 ? 4.7e-7 * p.splits : 0.0));
+    if (us > 0.95 * other) h.ok = false;
     return h;
 }
 

@@ -111,9 +111,15 @@ WGRAD_CASES = {
     "odd": ((3, 33, 31), (wl.conv(15, 3, pad=1, relu=True), wl.conv(20, 3, pad=1, relu=True),
                           wl.conv(36, 5, pad=2, groups=2, relu=True), wl.conv(12, 2),
                           wl.maxpool(3, 3), wl.fc(3)), 4, 20, {2, 3}),
-    # a first layer of 8 channels with a 7x7 kernel, stride 2, an unpadded 5x5 layer
+    # a first layer of 8 channels with a 7x7 kernel, stride 2 (both on the implicit GEMM: too few
+    # channels and tiles), an unpadded 5x5 layer
     "strided": ((8, 24, 24), (wl.conv(16, 7, pad=3, relu=True), wl.conv(136, 3, stride=2, pad=1, relu=True),
-                              wl.conv(64, 5, relu=True), wl.maxpool(2, 2), wl.fc(5)), 32, 5, {0, 1, 2}),
+                              wl.conv(64, 5, relu=True), wl.maxpool(2, 2), wl.fc(5)), 32, 5, {2}),
+    # stride 2 and 7x7 kernels, output tiles of 32 and 64 channels
+    "s2k3": ((16, 32, 32), (wl.conv(64, 3, stride=2, pad=1, relu=True), wl.fc(3)), 16, 24, {0}),
+    "s2k5": ((16, 32, 32), (wl.conv(16, 5, stride=2, pad=2, relu=True), wl.fc(3)), 16, 24, {0}),
+    "s2k7": ((16, 24, 24), (wl.conv(128, 7, stride=2, pad=3, relu=True), wl.fc(3)), 8, 16, {0}),
+    "k7": ((16, 12, 12), (wl.conv(16, 7, pad=3, relu=True), wl.fc(3)), 8, 32, {0}),
     # padded first layers (implicit GEMM)
     "first32": ((3, 33, 31), (wl.conv(20, 3, pad=1, relu=True), wl.maxpool(3, 2), wl.fc(3)), 4, 40, set()),
     "first64": ((5, 41, 43), (wl.conv(76, 3, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 95, set()),
@@ -145,9 +151,12 @@ OTHERWISE = {
     # a layer that closes its images to 1 x 1: 49 taps of its data gradient for one inside dy
     "closing": ((3, 7, 7), (wl.conv(128, 3, pad=1, relu=True), wl.conv(128, 7, relu=True), wl.fc(3)),
                 4, 256, {("dgrad", 1)}),
-    # 8 input channels in 64-row blocks at stride 2
+    # 8 input channels in 64-row blocks at stride 2, and in the weight gradient's 16-channel fragments
     "stride2c8": ((3, 22, 22), (wl.conv(8, 3, pad=1, relu=True), wl.conv(192, 3, stride=2, pad=1, relu=True),
-                                wl.maxpool(2, 2), wl.fc(3)), 8, 40, {("dgrad", 1)}),
+                                wl.maxpool(2, 2), wl.fc(3)), 8, 40, {("dgrad", 1), ("wgrad", 1)}),
+    # wide images: most of a weight gradient's window is loaded without the prefetch
+    "wide52": ((3, 52, 52), (wl.conv(64, 3, pad=1, relu=True), wl.conv(32, 3, relu=True), wl.maxpool(4, 4),
+                             wl.fc(3)), 2, 30, {("wgrad", 1)}),
 }
 
 
