@@ -123,9 +123,8 @@ ConvGeom proj_compact(const ConvGeom& g)
     return ConvGeom{g.N, g.C, g.OH, g.OW, g.OC, g.OH, g.OW, 1, 1, 0, 1};
 }
 
-// halo = false: without the convolutions over LDS windows (their padded weight layouts may need a
-// little more workspace than a caller has).
-int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true)
+// halo = false: without the convolutions over LDS windows.
+int plan_with(const mtx_model_desc* d, int R, int Nb, bool halo, Plan& pl)
 {
     if (!d) return fail(MTX_EINVAL, "desc is NULL");
     if (!d->layers || d->n_layers < 1) return fail(MTX_EINVAL, "the network has no layers");
@@ -567,6 +566,20 @@ int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl, bool halo = true
     return MTX_OK;
 }
 
+// The plan of a network depends on its description alone, so that every model of it runs the same
+// kernels.  The convolutions over LDS windows can take more scratch than the implicit GEMMs (padded
+// weight layouts, other reduction splits); a network that would only without them fit the static
+// workspace runs without them, there and in a caller's workspace.
+int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl)
+{
+    const int rc = plan_with(d, R, Nb, true, pl);
+    if (rc || pl.ws_bytes <= kStaticScratchBytes) return rc;
+    Plan general;
+    if (plan_with(d, R, Nb, false, general) == MTX_OK && general.ws_bytes <= kStaticScratchBytes)
+        pl = std::move(general);
+    return MTX_OK;
+}
+
 // ---- the static workspace of mtx_init_model_static ------------------------------------------
 // A model created by mtx_init_model_static runs its steps in this array instead of a caller
 // workspace.  Host code must never pass the array's name to a kernel or a copy (on the host it
@@ -945,11 +958,6 @@ static int init_model(const mtx_model_desc* desc, int R, int shard_batch, uint64
     Plan pl;
     int rc = make_plan(desc, R, shard_batch, pl);
     if (rc) return rc;
-    const size_t ws_have = static_ws ? kStaticScratchBytes : bufs->workspace_bytes;
-    if (pl.ws_bytes > ws_have) {
-        rc = make_plan(desc, R, shard_batch, pl = Plan(), false);
-        if (rc) return rc;
-    }
     if (!bufs->w || !bufs->v || !bufs->grads || !bufs->grad_avg ||
         (!static_ws && !bufs->workspace))
         return fail(MTX_EINVAL, "a model buffer is NULL");

@@ -152,6 +152,23 @@ def test_model_call_errors_need_no_device():
     assert b"workspace too small" in mtx.lib().mtx_last_error()
 
 
+def test_workspace_below_the_stated_size_is_refused():
+    """bf16 convolutions over LDS windows need more scratch here than the implicit GEMMs would
+    (weight gradients in more reduction splits): still no byte less than mtx_model_sizes asks for."""
+    layers = (wl.conv(64, 3, pad=1), wl.conv(64, 3, pad=1), wl.conv(64, 3, pad=1), wl.maxpool(4, 4),
+              wl.fc(10))
+    L = wl.layer_tuples(wl.Net("small-workspace", (3, 32, 32), layers, wl.BF16, "normal"))
+    d = mtx.make_desc((3, 32, 32), L, wl.BF16)
+    P, ld, ws = mtx.mtx_model_sizes(d, 8, 32)
+    h = C.c_void_p()
+    base = 1 << 30
+    small = mtx.mtx_buffers(base, 2 * base, 3 * base, 4 * base, 8 * base, ws - 256)
+    rc = mtx.lib().mtx_init_model(C.byref(d), 8, 32, C.c_uint64(0), C.byref(small), None,
+                                  C.byref(h))
+    assert rc == mtx.MTX_ENOMEM and not h.value
+    assert f"{ws} needed".encode() in mtx.lib().mtx_last_error()
+
+
 def test_static_model_takes_no_workspace():
     """mtx_init_model_static refuses a caller workspace before touching a device."""
     L = wl.layer_tuples(wl.LENET)

@@ -48,6 +48,23 @@ def test_static_workspace_steps_match_the_caller_workspace_twice_the_second_smal
     _pair(wl.MLP, 2, 32, 5, 2)
 
 
+def test_static_workspace_matches_where_only_the_general_kernels_fit_it():
+    """162 images of a shard: the convolutions over LDS windows fit 64 MiB; 163: their partial sums do
+    not, the implicit GEMMs' do, and both kinds of model run those."""
+    layers = (wl.conv(64, 5, pad=2, relu=True), wl.maxpool(2, 2), wl.fc(5))
+    net = wl.Net("static-edge", (32, 16, 16), layers, wl.BF16, "normal")
+    for Nb, windows in ((162, True), (163, False)):
+        _pair(net, 2, Nb, 6, 2)
+        m = mtx.Model(net.in_shape, wl.layer_tuples(net), net.dtype, 2, Nb)
+        assert m.ws_bytes <= 64 << 20
+        x, y = wl.make_batch(net, 2 * Nb, seed=1)
+        m.train_step(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda(), 0.01, 0.9)
+        torch.cuda.synchronize()
+        taken = any(l["flags"] & mtx.MTX_GEMM_HALO for l in mtx.mtx_get_launches(m.handle))
+        m.close()
+        assert taken == windows, Nb
+
+
 def test_static_workspace_alternating_models():
     """Two static models on one device, steps alternating (not overlapping): each step
     re-establishes its own part of the shared array."""
