@@ -16,7 +16,9 @@
 //
 // Every output's products are added in the order of the implicit GEMM (taps ascending, channels
 // ascending, 32 per matrix instruction, in the same lanes), so the results are the same bits;
-// reductions that the implicit GEMM splits keep it.
+// reductions that the implicit GEMM splits keep it.  Data gradients of unpadded layers, where the
+// alternative is the col product (a sum per tap, then the taps), are this one chain here: the same
+// error against 64 bits (3e-5 of the values round the other way on either).
 //
 // Measured per launch, implicit GEMM -> this kernel: 27 x 27 images, 5 x 5, 2 groups of 48 -> 128
 // channels, batch 256 (115 GFLOP) 152 -> 110 us forward, 193 -> 158 us data gradient; 13 x 13,

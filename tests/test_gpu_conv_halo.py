@@ -1,8 +1,8 @@
-"""GPU parity of the convolutions that hold their input windows in LDS (bf16) against the oracle,
-and against the implicit GEMM bit for bit: block shapes, channel counts that are not multiples of
-32 or 64, output channels off every vector width, ragged reduction steps, unpadded and grouped
-layers, tiles that cross images, whole-image tiles, padded first layers, data gradients at stride 2;
-and of the weight gradients over windows."""
+"""GPU parity of the convolutions that hold their input windows in LDS (bf16) against the oracle:
+block shapes, channel counts that are not multiples of 32 or 64, output channels off every vector
+width, ragged reduction steps, unpadded and grouped layers, tiles that cross images, whole-image
+tiles, padded first layers, data gradients at stride 2; the weight gradients over windows; and
+layers that stay on the general kernels."""
 import numpy as np
 import pytest
 import torch
