@@ -905,15 +905,15 @@ void destroy_streams(mtx_model* m)
 }  // namespace
 
 namespace mtx {
-void note_gemm(int fp, int fq, int bk, int splits, int flags)
+void note_gemm(int rows, int cols, int bk, int splits, int flags)
 {
     const RecordCtx& r = g_rec;
     if (!r.m) return;
     mtx_launch_info li{};
     std::snprintf(li.site, sizeof li.site, "%s", r.name);
     li.layer = r.layer;
-    li.tile_rows = 32 * fp;
-    li.tile_cols = 32 * fq;
+    li.tile_rows = rows;
+    li.tile_cols = cols;
     li.k_tile = bk;
     li.splits = splits;
     li.flags = flags;

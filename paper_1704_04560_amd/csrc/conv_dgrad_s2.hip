@@ -306,7 +306,7 @@ hipError_t conv_dgrad_s2(const ConvGeom& g, const HaloPlan& h, const void* dy, c
     }
     a.PT = halo_cdiv(a.cg, BP);
     const dim3 grid((unsigned)(tiles * a.PT * a.G));
-    note_gemm(BP / 32, BQ / 32, 32, 1, kGemmHalo);
+    note_gemm(BP, BQ, 32, 1, kGemmHalo);
     if (h.shape) hipLaunchKernelGGL((conv_dgrad_s2_kernel<2, 4, 4>), grid, dim3(512), (size_t)h.lds, s, a);
     else hipLaunchKernelGGL((conv_dgrad_s2_kernel<2, 2, 4>), grid, dim3(512), (size_t)h.lds, s, a);
     return hipGetLastError();

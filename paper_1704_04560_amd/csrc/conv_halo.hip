@@ -464,7 +464,7 @@ static void launch_halo(HaloArgs& a, const HaloPlan& h, bool bwd, hipStream_t s)
     a.PT = halo_cdiv(a.P, BP);
     const dim3 grid((unsigned)(halo_cdiv(a.Q, a.tile) * a.PT * a.G)), block(64 * NW);
     const size_t lds = (size_t)h.lds + (a.cg % 64 || a.row ? (size_t)(h.ks + 2) * 32 : 0);
-    note_gemm(BP / 32, BQ / 32, 32, 1, kGemmHalo);
+    note_gemm(BP, BQ, 32, 1, kGemmHalo);
     auto go = [&](auto bwd_, auto mode) {
         hipLaunchKernelGGL((conv_halo_kernel<NW, FP, WP, FQ, decltype(bwd_)::value, decltype(mode)::value>),
                            grid, block, lds, s, a);

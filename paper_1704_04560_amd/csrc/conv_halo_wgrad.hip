@@ -420,7 +420,7 @@ static void launch_wgrad(const HaloWArgs& a, const HaloWPlan& h, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.R * a.splits * a.G * a.cot * a.ubs));
     const size_t lds = (size_t)h.xlds + 128 * (32 * FA + 32) + 512 + halo_w_nx(K * NG * FA) * 2048;
-    note_gemm(FA / 2, 2, 32, a.splits, kGemmHalo | kGemmInterleaved);
+    note_gemm(16 * FA, 64 * NG * K, 32, a.splits, kGemmHalo | kGemmInterleaved);
     if (a.vx == 8 && a.vdy == 8)
         hipLaunchKernelGGL((conv_halo_wgrad_kernel<K, NG, FA, true>), grid, dim3(256), lds, s, a);
     else

@@ -1333,15 +1333,15 @@ static hipError_t launch_tile(const GemmArgs& a, int gz, hipStream_t s)
         shm = sizeof(TabEnt) * (size_t)n;
     }
     if constexpr (PK == L_KD || QK == L_KD) {
-        note_gemm(FP, FQ, BK, a.splits, kGemmDirectLds);
+        note_gemm(32 * FP, 32 * FQ, BK, a.splits, kGemmDirectLds);
         hipLaunchKernelGGL((igemm_direct_kernel<Op, FP, FQ, BK, PK, QK>), grid, dim3(256), shm, s,
                            a);
     } else if constexpr (Interleave<Op>::value && sizeof(typename Op::TT) == 2) {
-        note_gemm(FP, FQ, BK, a.splits, kGemmInterleaved);
+        note_gemm(32 * FP, 32 * FQ, BK, a.splits, kGemmInterleaved);
         hipLaunchKernelGGL((igemm_kernel<Op, FP, FQ, BK, PK, QK, true>), grid, dim3(256), shm, s,
                            a);
     } else {
-        note_gemm(FP, FQ, BK, a.splits, FuseUpdate<Op>::value ? kGemmFusedUpdate : 0);
+        note_gemm(32 * FP, 32 * FQ, BK, a.splits, FuseUpdate<Op>::value ? kGemmFusedUpdate : 0);
         constexpr bool EPI_OK = RowEpi<Op>::value && FP == 4 && FQ == 4 && !FuseUpdate<Op>::value;
         if constexpr (EPI_OK) {
             if (a.Kdim <= kEpi8MaxK && a.splits <= 1) {

@@ -164,7 +164,7 @@ constexpr int kGemmInterleaved = 1;  // the interleaved scheduling order of igem
 constexpr int kGemmDirectLds = 2;    // an operand loaded straight into LDS (igemm_direct_kernel)
 constexpr int kGemmFusedUpdate = 4;  // the weight gradient fused with the average + update
 constexpr int kGemmHalo = 8;         // input windows in LDS, read by every tap (conv_halo.hip)
-void note_gemm(int fp, int fq, int bk, int splits, int flags);
+void note_gemm(int rows, int cols, int bk, int splits, int flags);
 
 // elementwise.hip
 

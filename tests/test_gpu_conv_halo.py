@@ -193,7 +193,7 @@ def test_padding_reads_zeros_in_every_channel():
              if l["flags"] & mtx.MTX_GEMM_HALO and l["site"] == "fwd"]
     out = model.layer_output(0).reshape(B, OC, 6, 6)
     model.close()
-    assert tiles == [(192, 160)]
+    assert tiles == [(192, 176)]
 
     def bf16(a):
         return torch.from_numpy(np.ascontiguousarray(a)).bfloat16().double()
