@@ -196,31 +196,45 @@ __global__ __launch_bounds__(512, 4) void conv_dgrad_s2_kernel(const HaloS2Args 
     }
     u32x4 mk[NO];
     int idx[NO];
+    auto mask_rows = [&](auto width) {
+        constexpr int W = decltype(width)::value;
 #pragma unroll
-    for (int t = 0; t < NO; ++t) {
-        const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
-        idx[t] = q0 + q <= q1 && g * 8 < pn ? out_at(q0 + q) + g * 8 : -1;
-        if (a.mask && a.vout > 1) mk[t] = halo_row_load(bm, a.vout, idx[t] >= 0, idx[t], pn - g * 8);
-    }
-    __syncthreads();
+        for (int t = 0; t < NO; ++t) {
+            const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
+            idx[t] = q0 + q <= q1 && g * 8 < pn ? out_at(q0 + q) + g * 8 : -1;
+            if constexpr (W > 1)
+                if (a.mask) mk[t] = halo_row_load<W>(bm, idx[t] >= 0, idx[t], pn - g * 8);
+        }
+    };
+    auto store_rows = [&](auto width) {
+        constexpr int W = decltype(width)::value;
 #pragma unroll
-    for (int t = 0; t < NO; ++t) {
-        if (idx[t] < 0) continue;
-        const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
-        u32x4 v = *reinterpret_cast<const u32x4*>(ot + q * OSTR + g * 8);
-        if (a.vout > 1) {
-            if (a.mask) v = halo_masked(v, mk[t]);
-            halo_row_store(a.dx + idx[t], a.vout, v, pn - g * 8);
-        } else {
+        for (int t = 0; t < NO; ++t) {
+            if (idx[t] < 0) continue;
+            const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
+            u32x4 v = *reinterpret_cast<const u32x4*>(ot + q * OSTR + g * 8);
+            if constexpr (W > 1) {
+                if (a.mask) v = halo_masked(v, mk[t]);
+                halo_row_store<W>(a.dx + idx[t], v, pn - g * 8);
+            } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if (g * 8 + e >= pn) break;
-                bf16_t b = (bf16_t)(v[e / 2] >> (16 * (e & 1)));
-                if (a.mask && !(bf16_to_f32(a.mask[idx[t] + e]) > 0.f)) b = 0;
-                a.dx[idx[t] + e] = b;
+                for (int e = 0; e < 8; ++e) {
+                    if (g * 8 + e >= pn) break;
+                    bf16_t b = (bf16_t)(v[e / 2] >> (16 * (e & 1)));
+                    if (a.mask && !(bf16_to_f32(a.mask[idx[t] + e]) > 0.f)) b = 0;
+                    a.dx[idx[t] + e] = b;
+                }
             }
         }
-    }
+    };
+    auto finish = [&](auto width) {
+        mask_rows(width);
+        __syncthreads();
+        store_rows(width);
+    };
+    if (a.vout == 8) finish(std::integral_constant<int, 8>{});
+    else if (a.vout == 4) finish(std::integral_constant<int, 4>{});
+    else finish(std::integral_constant<int, 1>{});
 }
 
 // ---- plan -------------------------------------------------------------------------------------

@@ -245,18 +245,23 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
     // channels with 16-byte stores (8-byte ones where the channels are a multiple of 4 only); the
     // data gradient's mask is read with them.
     constexpr int OSTR = BP + 8, GP = BP / 8, NO = (BQ * GP + NT - 1) / NT;
+    typedef std::integral_constant<int, 8> W8;
+    typedef std::integral_constant<int, 4> W4;
+    typedef std::integral_constant<int, 1> W1;
     const int pn = min(BP, a.P - p0);
     u32x4 mk[BWD ? NO : 1];
     if constexpr (BWD) {
         // the mask's latency passes while the tile goes to LDS
-        if (a.mask && a.vout > 1) {
+        auto mask_rows = [&](auto width) {
 #pragma unroll
             for (int t = 0; t < NO; ++t) {
                 const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
                 const int idx = (q0 + q) * a.OC + grp * a.P + p0 + g * 8;
-                mk[t] = halo_row_load(bm, a.vout, q0 + q <= q1, idx, pn - g * 8);
+                mk[t] = halo_row_load<decltype(width)::value>(bm, q0 + q <= q1, idx, pn - g * 8);
             }
-        }
+        };
+        if (a.mask && a.vout == 8) mask_rows(W8{});
+        else if (a.mask && a.vout == 4) mask_rows(W4{});
     }
     __syncthreads();
     bf16_t* ot = reinterpret_cast<bf16_t*>(lds);
@@ -284,25 +289,31 @@ __global__ __launch_bounds__(64 * NW, FP * FQ <= 16 ? 4 : 2) void conv_halo_kern
         }
     }
     __syncthreads();
+    auto store_rows = [&](auto width) {
+        constexpr int W = decltype(width)::value;
 #pragma unroll
-    for (int t = 0; t < NO; ++t) {
-        const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
-        if (q0 + q > q1 || q >= a.tile || g * 8 >= pn) continue;
-        u32x4 v = *reinterpret_cast<const u32x4*>(ot + q * OSTR + g * 8);
-        const long long idx = (long long)(q0 + q) * a.OC + grp * a.P + p0 + g * 8;
-        if (a.vout > 1) {
-            if (BWD && a.mask) v = halo_masked(v, mk[t]);
-            halo_row_store(a.y + idx, a.vout, v, pn - g * 8);
-        } else {
+        for (int t = 0; t < NO; ++t) {
+            const int q = (tid + t * NT) / GP, g = (tid + t * NT) % GP;
+            if (q0 + q > q1 || q >= a.tile || g * 8 >= pn) continue;
+            u32x4 v = *reinterpret_cast<const u32x4*>(ot + q * OSTR + g * 8);
+            const long long idx = (long long)(q0 + q) * a.OC + grp * a.P + p0 + g * 8;
+            if constexpr (W > 1) {
+                if (BWD && a.mask) v = halo_masked(v, mk[BWD ? t : 0]);
+                halo_row_store<W>(a.y + idx, v, pn - g * 8);
+            } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if (g * 8 + e >= pn) break;
-                bf16_t b = (bf16_t)(v[e / 2] >> (16 * (e & 1)));
-                if (BWD && a.mask && !(bf16_to_f32(a.mask[idx + e]) > 0.f)) b = 0;
-                a.y[idx + e] = b;
+                for (int e = 0; e < 8; ++e) {
+                    if (g * 8 + e >= pn) break;
+                    bf16_t b = (bf16_t)(v[e / 2] >> (16 * (e & 1)));
+                    if (BWD && a.mask && !(bf16_to_f32(a.mask[idx + e]) > 0.f)) b = 0;
+                    a.y[idx + e] = b;
+                }
             }
         }
-    }
+    };
+    if (a.vout == 8) store_rows(W8{});
+    else if (a.vout == 4) store_rows(W4{});
+    else store_rows(W1{});
 }
 
 // ---- plan -------------------------------------------------------------------------------------
