@@ -335,6 +335,9 @@ int plan_with(const mtx_model_desc* d, int R, int Nb, bool halo, Plan& pl)
         if (lp.kind == MTX_CONV && lp.run) {
             const ConvGeom gb{pl.B, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
             if (halo) lp.fhalo = conv_halo_run_plan(pl.dt, gb, lp.rg);
+            ConvGeom gs = gb;
+            gs.N = pl.Nb;
+            if (halo) lp.whalo = conv_halo_wgrad_run_plan(pl.dt, gs, lp.rg, pl.R);
             if (lp.fhalo.ok) {
                 j.kind = PREP_HALO_RUN;
                 j.n = (int)lp.fhalo.w_elems;
@@ -1410,6 +1413,9 @@ static int enqueue_step(mtx_model* m, const float* x, const int32_t* labels, flo
         } else if (lp.kind == MTX_CONV) {
             ConvGeom gs{pl.Nb, lp.c, lp.h, lp.w, lp.oc, lp.oh, lp.ow, lp.k, lp.s, lp.p, lp.g};
             HIP_TRY(launch_site(m, "wgrad", l, sw, [&] {
+                        if (lp.whalo.ok && lp.run)
+                            return conv_halo_wgrad_run(gs, lp.rg, lp.whalo, pl.R, in_l, dy, m->grads,
+                                                       ld, (long long)lp.w_off, part_wg, sw);
                         if (lp.whalo.ok)
                             return conv_halo_wgrad(gs, lp.whalo, pl.R, in_l, dy, m->grads, ld,
                                                    (long long)lp.w_off, part_wg, sw);

@@ -35,18 +35,23 @@ struct HaloWArgs {
     int N, C, H, W, OC, OH, OW, S, PD, G;
     int cg, og, Q, R;
     int ckg, stride, Hp, Wp, ngroups, cot, ubs, splits, tps, tiles, dy_off, pt_off, gt_off, vx, vdy, vec;
+    int KT, row, ru, Cp;  // kernel size; RUN: elements per padded row, groups per window row, channels of a pixel
     long long w_len;
     FastDiv fd_ohw, fd_ow, fd_hp, fd_wp, fd_ckg;
 };
 
+// LDS bytes of a position's 16 * fa values of dy (fa even): an odd multiple of 32
+constexpr int halo_w_dys(int fa) { return fa * 32 + 32; }
+
 // window granules per thread loaded ahead, as registers allow
 constexpr int halo_w_nx(int accs) { return accs > 36 ? 5 : 7; }
 
-// V8: both operands are loaded 16 bytes at a time.
-template <int K, int NG, int FA, bool V8>
+// V8: both operands are loaded 16 bytes at a time.  RUN: the padded first-layer input
+// (conv_wgrad_run): a group is 16 elements of one window row (K = 1 here; a.ru of them per row).
+template <int K, int NG, int FA, bool V8, bool RUN>
 __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs a)
 {
-    constexpr int U = K * NG, BQ = 128, CO = 16 * FA, DYS = CO * 2 + 32, DG = CO / 8;
+    constexpr int U = K * NG, BQ = 128, CO = 16 * FA, DYS = halo_w_dys(FA), DG = CO / 8;
     constexpr int ND = BQ * DG / 256, NX = halo_w_nx(U * FA);
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char* const sdy = lds + a.dy_off;
@@ -71,12 +76,18 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
 
     // the wave's kernel-row groups: group = ci16 * K + u; the block's window holds the channels
     // from its first group's on
-    const int g0 = (ub * 4 + wave) * NG, c16 = ub * 4 * NG / K;
+    const int g0 = (ub * 4 + wave) * NG, c16 = RUN ? 0 : ub * 4 * NG / K;
     int goff[NG];
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
-        const int g = min(g0 + i, a.ngroups - 1), ci = g / K, u = g - ci * K;
-        goff[i] = u * a.Wp * a.stride + (ci - c16) * 32;
+        const int g = min(g0 + i, a.ngroups - 1);
+        if constexpr (RUN) {
+            const int u = g / a.ru;
+            goff[i] = u * a.row * 2 + (g - u * a.ru) * 32;
+        } else {
+            const int ci = g / K, u = g - ci * K;
+            goff[i] = u * a.Wp * a.stride + (ci - c16) * 32;
+        }
     }
     const int cbase = c16 * 16;  // first input channel (in the group) of the window
 
@@ -95,7 +106,9 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
         const unsigned h0 = fdiv(a.fd_ow, (unsigned)w.q0 - n0 * (unsigned)(a.OH * a.OW));
         const unsigned h1 = fdiv(a.fd_ow, (unsigned)w.q1 - n1 * (unsigned)(a.OH * a.OW));
         w.row0 = (int)n0 * a.Hp + (int)h0 * a.S;
-        w.ngran = ((int)n1 * a.Hp + (int)h1 * a.S + K - w.row0) * a.Wp * a.ckg;
+        const int rows = (int)n1 * a.Hp + (int)h1 * a.S + a.KT - w.row0;
+        // (RUN: the last window of a row may read past it, into values that are not stored)
+        w.ngran = RUN ? rows * (a.row / 8) + a.ru * 2 : rows * a.Wp * a.ckg;
         return w;
     };
     // Granule t of a window: padded row pr, input offset within a row (kOOB: in the padding or
@@ -120,7 +133,7 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
     // (kept in LDS for the prefetched granules: src, and dst / 16 | pr << 16)
     int2* const gt = reinterpret_cast<int2*>(lds + a.gt_off);
 #pragma unroll
-    for (int s = 0; s < NX; ++s) {
+    for (int s = 0; s < NX && !RUN; ++s) {
         int pr, src, dst, c8;
         granule(tid + s * 256, pr, src, dst, c8);
         gt[tid + s * 256] = make_int2(src, dst >> 4 | pr << 16);
@@ -130,6 +143,11 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
         constexpr int VX = decltype(vx)::value;
 #pragma unroll
         for (int s = 0; s < NX; ++s) {
+            if constexpr (RUN) {  // the window is contiguous
+                const int t = tid + s * 256, off = (r * a.N * a.Hp + w.row0) * a.row + t * 8;
+                px[s] = __builtin_amdgcn_raw_buffer_load_b128(bx, t < w.ngran ? off * 2 : (int)kOOB, 0, 0);
+                continue;
+            }
             const int2 m = gt[tid + s * 256];
             const int rb = row_base(w, m.y >> 16);
             const bool ok = (tid + s * 256 < w.ngran) & (rb != (int)kOOB) & (m.x != (int)kOOB);
@@ -167,6 +185,12 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
     // window granules beyond the prefetched ones
     auto stage_rest = [&](const Tile& w) {
         for (int t = NX * 256 + tid; t < w.ngran; t += 256) {
+            if constexpr (RUN) {
+                const int off = (r * a.N * a.Hp + w.row0) * a.row + t * 8;
+                *reinterpret_cast<u32x4*>(lds + t * 16) =
+                    __builtin_amdgcn_raw_buffer_load_b128(bx, off * 2, 0, 0);
+                continue;
+            }
             int pr, src, dst, c8;
             granule(t, pr, src, dst, c8);
             const int rb = row_base(w, pr);
@@ -179,7 +203,11 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
     };
 
     f32x4 acc[U][FA];
-    float accb = 0.f;  // bias gradient: the wave's fragment of dy, this lane's positions
+    // bias gradient: the wave's fragments of dy (every fourth), this lane's positions
+    constexpr int NB = (FA + 3) / 4;
+    float accb[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) accb[b] = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -204,13 +232,15 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
         }
 #pragma unroll
         for (int s = 0; s < NX; ++s)
-            if (tid + s * 256 < w.ngran) *reinterpret_cast<u32x4*>(lds + ((gt[tid + s * 256].y & 0xffff) << 4)) = px[s];
+            if (tid + s * 256 < w.ngran)
+                *reinterpret_cast<u32x4*>(lds + (RUN ? (tid + s * 256) << 4 : (gt[tid + s * 256].y & 0xffff) << 4)) = px[s];
         stage_rest(w);
         if (tid < BQ) {  // window origin of every position (past the end: the last one's, dy is 0)
             const unsigned q = (unsigned)min(w.q0 + tid, w.q1);
             const unsigned n = fdiv(a.fd_ohw, q), p = q - n * (unsigned)(a.OH * a.OW);
             const unsigned h = fdiv(a.fd_ow, p), ow = p - h * (unsigned)a.OW;
-            pt[tid] = (((int)n * a.Hp + (int)h * a.S - w.row0) * a.Wp + (int)ow * a.S) * a.stride;
+            pt[tid] = RUN ? (((int)n * a.Hp + (int)h * a.S - w.row0) * a.row + (int)ow * a.S * a.Cp) * 2
+                          : (((int)n * a.Hp + (int)h * a.S - w.row0) * a.Wp + (int)ow * a.S) * a.stride;
         }
         __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
         if (t + 1 < t1) {
@@ -250,9 +280,9 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
             if (bias) {
 #pragma unroll
                 for (int j = 0; j < FA; ++j)
-                    if (wave == j)
+                    if (wave == (j & 3))
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) accb += bf16_to_f32((bf16_t)fd[j][e]);
+                        for (int e = 0; e < 8; ++e) accb[j >> 2] += bf16_to_f32((bf16_t)fd[j][e]);
             }
         }
     }
@@ -266,7 +296,22 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
         const int co = co0 + j * 16 + lr;
         if (co >= a.og) continue;
         float* const wrow = row + (long long)(grp * a.og + co) * a.cg * KK;
-        if constexpr (NG == K) {
+        if constexpr (RUN) {
+            // element j = v * Cp + ci of window row u
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                const int g = g0 + i, u = g / a.ru, jb = (g - u * a.ru) * 16 + lg * 4;
+                if (g >= a.ngroups) continue;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int v = (jb + e) / a.Cp, ci = jb + e - v * a.Cp;
+                    if (v < a.KT && ci < a.cg)
+                        row[((long long)co * a.cg + ci) * a.KT * a.KT + u * a.KT + v] = acc[i][j][e];
+                }
+            }
+            continue;
+        }
+        if constexpr (NG == K && !RUN) {
             // every tap of 4 input channels: 4*K*K consecutive values
             const int ci = g0 / K * 16 + lg * 4;
             if (g0 < a.ngroups && a.vec && ci < a.cg) {
@@ -294,10 +339,14 @@ __global__ __launch_bounds__(256, 2) void conv_halo_wgrad_kernel(const HaloWArgs
         }
     }
     if (bias) {  // the four lane groups hold different positions
-        accb += __shfl_xor(accb, 16);
-        accb += __shfl_xor(accb, 32);
-        const int co = co0 + wave * 16 + lr;
-        if (lg == 0 && wave < FA && co < a.og) row[a.w_len + grp * a.og + co] = accb;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            float v = accb[b];
+            v += __shfl_xor(v, 16);
+            v += __shfl_xor(v, 32);
+            const int j = b * 4 + wave, co = co0 + j * 16 + lr;
+            if (lg == 0 && j < FA && co < a.og) row[a.w_len + grp * a.og + co] = v;
+        }
     }
 }
 
@@ -322,6 +371,25 @@ __global__ __launch_bounds__(256) void halo_wgrad_reduce(const float* __restrict
 }
 
 // ---- plan -------------------------------------------------------------------------------------
+namespace {
+// Reduction splits of a planned launch: as few as give every compute unit a block, of at least three
+// tiles (with two, 88 channels of a small layer took 16 to 18 us against the implicit GEMM's 14.6):
+// the partial rows that a second block per unit would write and read back cost more than it gains
+// (two per unit: CIFAR step 828 -> 863 us, residual block 558 -> 580, AlexNet 2370 -> 2427), and the
+// data-gradient chain on the other stream runs beside one.
+void choose_splits(HaloWPlan& h, int R, int G)
+{
+    const long long base = (long long)R * G * h.cot * h.ubs;
+    h.ld = (h.n + 3) / 4 * 4;
+    long long splits = (256 + base - 1) / base;
+    splits = std::min<long long>(splits, std::max(1, h.tiles / 3));
+    while (splits > 1 && splits * R * h.ld > (64ll << 20)) --splits;
+    h.tps = halo_cdiv(h.tiles, (int)splits);
+    h.splits = halo_cdiv(h.tiles, h.tps);
+    if (base * h.splits < 192) h.ok = false;
+}
+}  // namespace
+
 HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R)
 {
     HaloWPlan h{};
@@ -362,7 +430,7 @@ HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R)
         int stride = span * 32;
         while (stride % 64 != 32) stride += 16;
         const long long xl = (long long)rows * h.Wp * stride;
-        if (xl + 128 * (32 * h.fa + 32) + 512 + halo_w_nx(g.K * ng * h.fa) * 2048 > kHaloMaxLds) continue;
+        if (xl + 128 * halo_w_dys(h.fa) + 512 + halo_w_nx(g.K * ng * h.fa) * 2048 > kHaloMaxLds) continue;
         // (a wave with fewer groups reads its dy fragments for fewer products)
         const double score = (double)h.ngroups / (ubs * 4 * ng) * (1.0 - 0.3 / (ng * g.K));
         if (score > best) {
@@ -372,20 +440,8 @@ HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R)
         }
     }
     if (!h.ok) return h;
-    const long long base = (long long)R * g.G * h.cot * h.ubs;
     h.n = (long long)g.OC * cg * g.K * g.K + g.OC;
-    h.ld = (h.n + 3) / 4 * 4;
-    // As few as give every compute unit a block, of at least three tiles (with two, 88 channels of a
-    // small layer took 16 to 18 us against the implicit GEMM's 14.6): the partial rows that a second
-    // block per unit would write and read back cost more than it gains (two per unit: CIFAR step 828 ->
-    // 863 us, residual block 558 -> 580, AlexNet 2370 -> 2427), and the data-gradient chain on the other
-    // stream runs beside one.
-    long long splits = (256 + base - 1) / base;
-    splits = std::min<long long>(splits, std::max(1, h.tiles / 3));
-    while (splits > 1 && splits * R * h.ld > (64ll << 20)) --splits;
-    h.tps = halo_cdiv(h.tiles, (int)splits);
-    h.splits = halo_cdiv(h.tiles, h.tps);
-    if (base * h.splits < 192) h.ok = false;
+    choose_splits(h, R, g.G);
     // Estimated time of both (see gemm_us).  Here, per tile of the busiest compute unit: its products or
     // the latency of its loads, the fragment reads, window granules past the prefetched ones, narrow
     // loads; then the splits' rows.  The implicit GEMM pays for narrow loads too, and for its scattered
@@ -394,7 +450,7 @@ HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R)
     // against 173) are left to it: of 720 drawn layers 239 were slower here, with this rule 29 (49.1
     // -> 48.8 ms in sum; 55.6 all on the implicit GEMM, 51.2 without the rule).
     const int accs = g.K * h.ng * h.fa, odd = cg % 4 || og % 4 ? 2 : cg % 8 || og % 8 ? 1 : 0;
-    const double n = (double)((base * h.splits + 255) / 256), gran = (double)h.xlds / h.stride * h.ckg / 256;
+    const double n = (double)(((long long)R * g.G * h.cot * h.ubs * h.splits + 255) / 256), gran = (double)h.xlds / h.stride * h.ckg / 256;
     const double tile = std::max(0.0417 * accs * n, 1.86 * std::ceil(n / 2)) +
                         n * (0.048 * (g.K * h.ng + h.fa) + 0.106 * std::max(0.0, gran - halo_w_nx(accs)) +
                              (odd == 2 ? 0.124 : odd ? 0.0165 : 0.0) * (gran + h.fa));
@@ -410,40 +466,81 @@ HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R)
     return h;
 }
 
+HaloWPlan conv_halo_wgrad_run_plan(int dt, const ConvGeom& g, const RunGeom& r, int R)
+{
+    HaloWPlan h{};
+    const long long Q = (long long)g.N * g.OH * g.OW;
+    if (dt != DT_BF16 || g.G != 1 || g.OC % 4 || Q > (1ll << 30)) return h;
+    h.Hp = r.Hp;
+    h.tiles = (int)((Q + 127) / 128);
+    h.fa = g.OC <= 32 ? 2 : 4;
+    h.cot = halo_cdiv(g.OC, 16 * h.fa);
+    h.ru = halo_cdiv(r.RUN, 16);
+    h.ngroups = g.K * h.ru;
+    int rows = 0;
+    // (tiles repeat their place in an image)
+    const long long period = (long long)g.OH * g.OW / std::__gcd(128, g.OH * g.OW) * 128;
+    for (long long q0 = 0; q0 < std::min(Q, period); q0 += 128) {
+        const long long q1 = std::min<long long>(q0 + 128, Q) - 1;
+        auto row = [&](long long q) { return q / (g.OH * g.OW) * r.Hp + q % (g.OH * g.OW) / g.OW * g.S; };
+        rows = std::max(rows, (int)(row(q1) - row(q0)) + g.K);
+    }
+    h.xlds = (rows * r.Wp * r.Cp + h.ru * 16) * 2;
+    // Window rows of at most two groups, that is small kernels; with more, the sums of a wave leave one
+    // wave per SIMD and a quarter of its groups idle (11 x 11, stride 4, 96 channels: 190 us against the
+    // implicit GEMM's 179).
+    h.ng = 2;
+    h.ubs = halo_cdiv(h.ngroups, 4 * h.ng);
+    h.ok = h.ru <= 2 && h.xlds + 128 * halo_w_dys(h.fa) + 512 <= kHaloMaxLds;
+    if (!h.ok) return h;
+    h.n = (long long)g.OC * g.C * g.K * g.K + g.OC;
+    h.run = true;
+    choose_splits(h, R, 1);
+    // Estimated time of both (see gemm_us): tiles of few products wait for their loads, so that a
+    // small layer in one block per unit gains (32 x 32, 3 -> 64 channels, 3 x 3, batch 512: 43 -> 41 us
+    // alone, CIFAR step 830 -> 808), one of several channel tiles does not (3 -> 256, batch 256: 56 -> 65
+    // us).  Of 52 drawn layers 37 were slower here (2245 -> 2579 us in sum), with this rule 2 (by 6 us).
+    const double n = std::ceil((double)R * h.cot * h.ubs * h.splits / 256);
+    const double us = 16 + h.tps * (std::max(0.047 * h.fa * n, 1.05 * std::ceil(n / 2)) + 0.08 * n * (2 + h.fa));
+    const GemmDims d = conv_wgrad_run_dims(dt, g, r, R);
+    if (us > 0.95 * gemm_us(d, plan_for(dt, d), 17.2, 0.018, 0.028)) h.ok = false;
+    return h;
+}
+
 size_t conv_halo_wgrad_partial(const HaloWPlan& h, int R)
 {
     return h.ok && h.splits > 1 ? (size_t)h.splits * R * h.ld : 0;
 }
 
-template <int K, int NG, int FA>
+template <int K, int NG, int FA, bool RUN = false>
 static void launch_wgrad(const HaloWArgs& a, const HaloWPlan& h, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.R * a.splits * a.G * a.cot * a.ubs));
-    const size_t lds = (size_t)h.xlds + 128 * (32 * FA + 32) + 512 + halo_w_nx(K * NG * FA) * 2048;
+    const size_t lds = (size_t)h.xlds + 128 * halo_w_dys(FA) + 512 + (RUN ? 0 : halo_w_nx(K * NG * FA) * 2048);
     note_gemm(16 * FA, 64 * NG * K, 32, a.splits, kGemmHalo | kGemmInterleaved);
     if (a.vx == 8 && a.vdy == 8)
-        hipLaunchKernelGGL((conv_halo_wgrad_kernel<K, NG, FA, true>), grid, dim3(256), lds, s, a);
+        hipLaunchKernelGGL((conv_halo_wgrad_kernel<K, NG, FA, true, RUN>), grid, dim3(256), lds, s, a);
     else
-        hipLaunchKernelGGL((conv_halo_wgrad_kernel<K, NG, FA, false>), grid, dim3(256), lds, s, a);
+        hipLaunchKernelGGL((conv_halo_wgrad_kernel<K, NG, FA, false, RUN>), grid, dim3(256), lds, s, a);
 }
 
-hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const void* x, const void* dy,
-                           float* grads, long long ld, long long w_off, float* partial, hipStream_t s)
+// fields that both launchers set, the launch and the reduction
+static hipError_t run_wgrad(HaloWArgs& a, const ConvGeom& g, const HaloWPlan& h, int R, const void* x,
+                            const void* dy, float* grads, long long ld, long long w_off, float* partial,
+                            hipStream_t s)
 {
     if (!h.ok || (h.splits > 1 && !partial)) return hipErrorInvalidValue;
-    HaloWArgs a{};
     a.x = static_cast<const bf16_t*>(x); a.dy = static_cast<const bf16_t*>(dy);
-    a.x_bytes = (unsigned)((size_t)R * g.N * g.C * g.H * g.W * 2);
     a.dy_bytes = (unsigned)((size_t)R * g.N * g.OC * g.OH * g.OW * 2);
     a.N = g.N; a.C = g.C; a.H = g.H; a.W = g.W; a.OC = g.OC; a.OH = g.OH; a.OW = g.OW;
-    a.S = g.S; a.PD = g.PD; a.G = g.G;
+    a.S = g.S; a.PD = g.PD; a.G = g.G; a.KT = g.K;
     a.cg = g.C / g.G; a.og = g.OC / g.G; a.Q = g.N * g.OH * g.OW; a.R = R;
     a.ckg = h.ckg; a.stride = h.stride; a.Hp = h.Hp; a.Wp = h.Wp; a.ngroups = h.ngroups;
     a.cot = h.cot; a.ubs = h.ubs; a.splits = h.splits; a.tps = h.tps; a.tiles = h.tiles;
     a.dy_off = h.xlds;
-    a.pt_off = h.xlds + 128 * (32 * h.fa + 32);
+    a.pt_off = h.xlds + 128 * halo_w_dys(h.fa);
     a.gt_off = a.pt_off + 512;
-    a.vx = a.cg % 8 == 0 ? 8 : a.cg % 4 == 0 ? 4 : 1;
+    a.vx = h.run || a.cg % 8 == 0 ? 8 : a.cg % 4 == 0 ? 4 : 1;
     a.vdy = a.og % 8 == 0 ? 8 : a.og % 4 == 0 ? 4 : 1;
     if (a.vx != 8 || a.vdy != 8) {  // one kernel variant for every narrower load
         a.vx = std::min(a.vx, 4);
@@ -459,8 +556,10 @@ hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const v
     a.fd_hp = make_fastdiv((unsigned)h.Hp);
     a.fd_wp = make_fastdiv((unsigned)h.Wp);
     a.fd_ckg = make_fastdiv((unsigned)h.ckg);
-    const int id = g.K * 100 + h.ng * 10 + h.fa;
+    const int id = (h.run ? 0 : g.K) * 100 + h.ng * 10 + h.fa;
     switch (id) {
+    case 24: launch_wgrad<1, 2, 4, true>(a, h, s); break;
+    case 22: launch_wgrad<1, 2, 2, true>(a, h, s); break;
     case 244: launch_wgrad<2, 4, 4>(a, h, s); break;
     case 242: launch_wgrad<2, 4, 2>(a, h, s); break;
     case 224: launch_wgrad<2, 2, 4>(a, h, s); break;
@@ -485,6 +584,24 @@ hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const v
     hipLaunchKernelGGL(halo_wgrad_reduce, dim3((unsigned)((h.ld / 4 + 255) / 256), R), dim3(256), 0, s,
                        partial, h.splits, R, h.ld, h.n, grads, ld, w_off);
     return hipGetLastError();
+}
+
+hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const void* x, const void* dy,
+                           float* grads, long long ld, long long w_off, float* partial, hipStream_t s)
+{
+    HaloWArgs a{};
+    a.x_bytes = (unsigned)((size_t)R * g.N * g.C * g.H * g.W * 2);
+    return run_wgrad(a, g, h, R, x, dy, grads, ld, w_off, partial, s);
+}
+
+hipError_t conv_halo_wgrad_run(const ConvGeom& g, const RunGeom& rg, const HaloWPlan& h, int R,
+                               const void* xp, const void* dy, float* grads, long long ld,
+                               long long w_off, float* partial, hipStream_t s)
+{
+    HaloWArgs a{};
+    a.x_bytes = (unsigned)((size_t)R * g.N * rg.Hp * rg.Wp * rg.Cp * 2);
+    a.row = rg.Wp * rg.Cp; a.ru = h.ru; a.Cp = rg.Cp;
+    return run_wgrad(a, g, h, R, xp, dy, grads, ld, w_off, partial, s);
 }
 
 }  // namespace mtx

@@ -355,6 +355,8 @@ struct HaloWPlan {
     int fa, ng;               // 16-channel fragments of dy, kernel-row groups per wave
     int cot, ubs, ngroups;    // output channel tiles, group tiles, groups (ci16, u)
     int ckg, stride, Hp, Wp, xlds;
+    int ru;                   // padded first layer (run): groups per window row
+    bool run;
     int tiles, tps, splits;   // 128-position tiles of a shard, per split, splits
     long long n, ld;          // values of a gradient row, padded partial row
 };
@@ -372,6 +374,11 @@ hipError_t conv_dgrad_s2(const ConvGeom& g, const HaloPlan& h, const void* dy, c
                          const void* mask, void* dx, hipStream_t s);
 // The forward of a padded first layer (conv_fwd_run), weights PREP_HALO_RUN.
 HaloPlan conv_halo_run_plan(int dt, const ConvGeom& g, const RunGeom& r);
+// The weight gradient of a padded first layer (conv_wgrad_run).
+HaloWPlan conv_halo_wgrad_run_plan(int dt, const ConvGeom& g, const RunGeom& r, int R);
+hipError_t conv_halo_wgrad_run(const ConvGeom& g, const RunGeom& rg, const HaloWPlan& h, int R,
+                               const void* xp, const void* dy, float* grads, long long ld,
+                               long long w_off, float* partial, hipStream_t s);
 hipError_t conv_halo_run(const ConvGeom& g, const RunGeom& r, const HaloPlan& h, const void* xp,
                          const void* w, const float* bias, bool relu, void* y, hipStream_t s);
 

@@ -120,7 +120,10 @@ WGRAD_CASES = {
     "s2k5": ((16, 32, 32), (wl.conv(16, 5, stride=2, pad=2, relu=True), wl.fc(3)), 16, 24, {0}),
     "s2k7": ((16, 24, 24), (wl.conv(128, 7, stride=2, pad=3, relu=True), wl.fc(3)), 8, 16, {0}),
     "k7": ((16, 12, 12), (wl.conv(16, 7, pad=3, relu=True), wl.fc(3)), 8, 32, {0}),
-    # padded first layers (implicit GEMM)
+    # padded first layers: output tiles of 64 and 32 channels
+    "firstw": ((3, 33, 31), (wl.conv(60, 3, pad=1, relu=True), wl.maxpool(3, 2), wl.fc(3)), 8, 64, {0}),
+    "firstw2": ((5, 32, 32), (wl.conv(20, 4, pad=2, relu=True), wl.maxpool(3, 2), wl.fc(3)), 8, 100, {0}),
+    # ... on the implicit GEMM
     "first32": ((3, 33, 31), (wl.conv(20, 3, pad=1, relu=True), wl.maxpool(3, 2), wl.fc(3)), 4, 40, set()),
     "first64": ((5, 41, 43), (wl.conv(76, 3, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 95, set()),
     "first2": ((3, 40, 42), (wl.conv(36, 2, stride=2, relu=True), wl.maxpool(2, 2), wl.fc(3)), 2, 120, set()),
