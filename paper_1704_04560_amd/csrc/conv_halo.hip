@@ -9,10 +9,12 @@
 // tap reads its fragments at an offset from the same origins.  Weights do not pass through LDS:
 // they are prepared fragment by fragment (1 KB per 16 rows and k step, in lane order), so that a
 // wave loads them straight into registers at the full 64 bytes per clock, one k step ahead.  The
-// main loop has no barrier.  What bounds it now is the latency of its fragment reads, which other
-// waves cover: 16 waves per compute unit (two blocks of 8) beat 8 to 12 with twice the products
-// per read (CIFAR 64-channel layers 56 -> 53 us), and images of 13 x 13, whose rows fill 11
-// column fragments, take a whole image per block.
+// main loop has no barrier.  What bounds it now is latency (weights from L2, fragments from LDS)
+// rather than a port: on the CIFAR and AlexNet layers the matrix cores are busy 24 to 45% of a launch,
+// LDS 15 to 32% (of which a fifth to a third are bank conflicts), and a wave waits 35 to 66% of its
+// cycles.  Other waves cover it: 16 waves per compute unit (two blocks of 8) beat 8 to 12 with twice
+// the products per read (CIFAR 64-channel layers 56 -> 53 us), and images of 13 x 13, whose rows fill
+// 11 column fragments, take a whole image per block.
 //
 // Every output's products are added in the order of the implicit GEMM (taps ascending, channels
 // ascending, 32 per matrix instruction, in the same lanes), so the results are the same bits;
@@ -420,7 +422,7 @@ HaloPlan conv_halo_plan(int dt, const ConvGeom& geom, bool bwd)
     if (plan_for(dt, bwd ? conv_dgrad_dims(dt, geom) : conv_fwd_dims(dt, geom)).splits > 1) return h;
     h.ckg = cg / 8;
     h.ks = halo_cdiv(g.K * g.K * h.ckg, 8) * 2;
-    h.stride = cg * 2;  // an odd multiple of 32 bytes: the fragment reads meet distinct banks
+    h.stride = cg * 2;  // an odd multiple of 32 bytes: neighbouring positions start in other banks
     while (h.stride % 64 != 32) h.stride += 16;
     auto lo = [&](long long q) {
         const int oh = (int)(q % img / g.OW);

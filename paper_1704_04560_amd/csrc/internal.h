@@ -275,12 +275,12 @@ hipError_t add_fwd(Dt dt, size_t n, const void* a, const void* b, void* y, bool 
 hipError_t add_bwd(Dt dt, size_t n, const void* dy, void* dx, const void* mask, bool mask_f32,
                    void* skip, const void* smask, bool smask_f32, hipStream_t s);
 // dy += skip where smask (the source's stored output, its ReLU) is positive; null: everywhere
-// The share of a 1x1 projection of stride g.S, held for the positions it reads: [N][OH][OW][C]
-// (C a multiple of a vector); smask as above, of the full size.
-hipError_t skip_add_strided(Dt dt, const ConvGeom& g, void* dy, const void* skip, const void* smask,
-                            bool smask_f32, hipStream_t s);
 hipError_t skip_add(Dt dt, size_t n, void* dy, const void* skip, const void* smask,
                     bool smask_f32, hipStream_t s);
+// The same for the share of a 1x1 projection of stride g.S, held for the positions it reads:
+// [N][OH][OW][C] (C a multiple of a vector); smask of the full size.
+hipError_t skip_add_strided(Dt dt, const ConvGeom& g, void* dy, const void* skip, const void* smask,
+                            bool smask_f32, hipStream_t s);
 
 // firstconv.hip: direct kernels for a first convolution with one input channel, stride 1,
 // a 3x3, 5x5 or 7x7 window and at most 32 output channels (a multiple of 4) whose image and
