@@ -111,6 +111,8 @@ struct Plan {
     size_t ws_bytes = 0;
 };
 
+constexpr double kOverlapFlops = 50e9;  // matrix work of a step from which its streams overlap
+
 // The 1x1 convolution of a projection shortcut (layer lp, source sp) over N images.
 ConvGeom proj_geom(const LayerPlan& lp, const LayerPlan& sp, int N)
 {
@@ -312,6 +314,21 @@ int plan_with(const mtx_model_desc* d, int R, int Nb, bool halo, Plan& pl)
                              first_conv_pool_ok(g0, p1.k);
     }
 
+    for (const LayerPlan& lp : pl.L) {
+        if (lp.w_len && lp.kind == MTX_ADDP) {
+            const double macs = (double)pl.B * lp.oh * lp.ow * lp.oc * pl.L[lp.src].oc;
+            pl.gemm_flops += 2.0 * macs * (lp.src >= pl.first_param ? 3 : 2);
+        } else if (lp.w_len && lp.kind != MTX_BN) {
+            const double macs = lp.kind == MTX_CONV
+                                    ? (double)pl.B * lp.oh * lp.ow * lp.oc * (lp.c / lp.g) * lp.k * lp.k
+                                    : (double)pl.B * lp.in_elems * lp.oc;
+            pl.gemm_flops += 2.0 * macs * (lp.need_dx ? 3 : 2);
+        }
+    }
+    // The weight gradients of a step with this much matrix work run on a second stream beside the
+    // data-gradient chain (see init_model).
+    const bool beside = pl.gemm_flops >= kOverlapFlops;
+
     // weight preparation jobs; every prepared tensor starts 16-byte aligned
     size_t pe = 0;
     int blocks = 0;
@@ -388,7 +405,7 @@ int plan_with(const mtx_model_desc* d, int R, int Nb, bool halo, Plan& pl)
             if (halo && lp.need_dx) lp.bhalo = conv_halo_plan(pl.dt, gb, true);
             ConvGeom gs = gb;
             gs.N = pl.Nb;
-            if (halo) lp.whalo = conv_halo_wgrad_plan(pl.dt, gs, pl.R);
+            if (halo) lp.whalo = conv_halo_wgrad_plan(pl.dt, gs, pl.R, beside);
             if (halo && lp.need_dx && !lp.bhalo.ok) lp.bhalo = conv_dgrad_s2_plan(pl.dt, gb);
             if (lp.bhalo.ok) {
                 lp.bw_off = halo_job(lp.bhalo, PREP_HALO_D);
@@ -510,15 +527,6 @@ int plan_with(const mtx_model_desc* d, int R, int Nb, bool halo, Plan& pl)
         // the first parameter layer's weight gradient runs on the caller's stream
         if ((int)i == pl.first_param) max_partial = std::max(max_partial, wgrad_partial);
         if (lp.w_len) pl.n_wgrad += 1;
-        if (lp.w_len && lp.kind == MTX_ADDP) {
-            const double macs = (double)pl.B * lp.oh * lp.ow * lp.oc * pl.L[lp.src].oc;
-            pl.gemm_flops += 2.0 * macs * (lp.src >= pl.first_param ? 3 : 2);
-        } else if (lp.w_len && lp.kind != MTX_BN) {
-            const double macs = lp.kind == MTX_CONV
-                                    ? (double)pl.B * lp.oh * lp.ow * lp.oc * (lp.c / lp.g) * lp.k * lp.k
-                                    : (double)pl.B * lp.in_elems * lp.oc;
-            pl.gemm_flops += 2.0 * macs * (lp.need_dx ? 3 : 2);
-        }
     }
     // A residual addition passes its output gradient to the previous layer unchanged when that
     // layer has no ReLU (its output is not read by any other addition): the previous layer then
@@ -1000,7 +1008,7 @@ static int init_model(const mtx_model_desc* desc, int R, int shard_batch, uint64
     // Measured on MI355X: running the weight gradients beside the data-gradient chain gains a
     // few percent when the step's matrix work is large (CIFAR-, AlexNet-sized steps) and loses
     // on small steps, whose kernels each fill the GPU on their own (LeNet).
-    m->overlap = m->pl.gemm_flops >= 50e9;
+    m->overlap = m->pl.gemm_flops >= kOverlapFlops;
 
     std::vector<float> w0;
     glorot_init_host(m->pl, seed, w0);

@@ -360,7 +360,8 @@ struct HaloWPlan {
     int tiles, tps, splits;   // 128-position tiles of a shard, per split, splits
     long long n, ld;          // values of a gradient row, padded partial row
 };
-HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R);
+// beside: the launch runs beside the data gradients of the layers below.
+HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R, bool beside);
 size_t conv_halo_wgrad_partial(const HaloWPlan& h, int R);
 hipError_t conv_halo_wgrad(const ConvGeom& g, const HaloWPlan& h, int R, const void* x, const void* dy,
                            float* grads, long long ld, long long w_off, float* partial, hipStream_t s);
