@@ -584,7 +584,8 @@ int plan_with(const mtx_model_desc* d, int R, int Nb, bool halo, Plan& pl)
 int make_plan(const mtx_model_desc* d, int R, int Nb, Plan& pl)
 {
     const int rc = plan_with(d, R, Nb, true, pl);
-    if (rc || pl.ws_bytes <= kStaticScratchBytes) return rc;
+    // (activations and inputs alone, which both plans have, may be too large)
+    if (rc || pl.ws_bytes <= kStaticScratchBytes || pl.prep_off > kStaticScratchBytes) return rc;
     Plan general;
     if (plan_with(d, R, Nb, false, general) == MTX_OK && general.ws_bytes <= kStaticScratchBytes)
         pl = std::move(general);
