@@ -458,7 +458,8 @@ HaloWPlan conv_halo_wgrad_plan(int dt, const ConvGeom& g, int R, bool beside)
     // against 173) are left to it: of 720 drawn layers 239 were slower here, with this rule 29 (49.1
     // -> 48.8 ms in sum; 55.6 all on the implicit GEMM, 51.2 without the rule).
     const int accs = g.K * h.ng * h.fa, odd = cg % 4 || og % 4 ? 2 : cg % 8 || og % 8 ? 1 : 0;
-    const double n = (double)(((long long)R * g.G * h.cot * h.ubs * h.splits + 255) / 256), gran = (double)h.xlds / h.stride * h.ckg / 256;
+    const double n = std::ceil((double)R * g.G * h.cot * h.ubs * h.splits / 256);
+    const double gran = (double)h.xlds / h.stride * h.ckg / 256;
     const double tile = std::max(0.0417 * accs * n, 1.86 * std::ceil(n / 2)) +
                         n * (0.048 * (g.K * h.ng + h.fa) + 0.106 * std::max(0.0, gran - halo_w_nx(accs)) +
                              (odd == 2 ? 0.124 : odd ? 0.0165 : 0.0) * (gran + h.fa));

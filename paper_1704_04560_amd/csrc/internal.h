@@ -335,8 +335,8 @@ hipError_t conv_dgrad_fused(const ConvGeom& g, const float* dy, const float* w, 
 
 // conv_halo.hip: bf16 stride-1 convolution forward and data gradient with the
 // input window of an output tile held in LDS; the products and their order are those of the
-// implicit GEMM, so the results are the same bits (not those of the col product).  conv_halo_plan tells whether a layer takes it
-// (ok) and how its weights are laid out (w_elems elements, PREP_HALO_F / PREP_HALO_D).
+// implicit GEMM, so the results are the same bits (not those of the col product).
+// conv_halo_plan tells whether a layer takes it (ok) and how its weights are laid out (w_elems elements, PREP_HALO_F / PREP_HALO_D).
 struct HaloPlan {
     bool ok;
     int shape;                // block shape (index into the kernel's list)
