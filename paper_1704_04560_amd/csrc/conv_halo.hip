@@ -10,9 +10,9 @@
 // they are prepared fragment by fragment (1 KB per 16 rows and k step, in lane order), so that a
 // wave loads them straight into registers at the full 64 bytes per clock, one k step ahead.  The
 // main loop has no barrier.  What bounds it now is latency (weights from L2, fragments from LDS)
-// rather than a port: on the CIFAR and AlexNet layers the matrix cores are busy 24 to 45% of a launch,
-// LDS 15 to 32% (of which a fifth to a third are bank conflicts), and a wave waits 35 to 66% of its
-// cycles.  Other waves cover it: 16 waves per compute unit (two blocks of 8) beat 8 to 12 with twice
+// rather than a port: on the CIFAR and AlexNet layers the matrix cores are busy 24 to 45% of a launch
+// (CIFAR's first layer 13%), LDS 15 to 32% (with 0.2 to 0.37 bank conflict cycles for an active one),
+// and a wave waits 34 to 67% of its cycles.  Other waves cover it: 16 waves per compute unit (two blocks of 8) beat 8 to 12 with twice
 // the products per read (CIFAR 64-channel layers 56 -> 53 us), and images of 13 x 13, whose rows fill
 // 11 column fragments, take a whole image per block.
 //

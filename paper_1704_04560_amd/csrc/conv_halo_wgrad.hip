@@ -15,8 +15,8 @@
 //
 // What bounds it: latency.  The plan launches about one block per compute unit (two would fit: a wave's
 // sums take 144 registers, but they double the partial rows, see choose_splits), so each SIMD has one
-// wave, and the staging between the tiles shows: matrix cores busy 17 to 28% on the CIFAR and AlexNet
-// layers, LDS 10 to 20%, waves waiting a third of their cycles.  Measured per launch, without the
+// wave, and the staging between the tiles shows: matrix cores busy 17 to 28% on the CIFAR, residual
+// and AlexNet layers (first layers 10%), LDS 10 to 20%, waves waiting a third of their cycles.  Measured per launch, without the
 // reductions: 27 x 27, 5 x 5, 2 groups of 48 -> 128, batch 256 in 8 shards 176 -> 139 us (6 splits; 4:
 // 169); 13 x 13, 256 -> 384 118 -> 108 us, 2 groups of 192 -> 192 115 -> 84 us; 32 x 32, 64 -> 64, batch
 // 512 114 -> 71 us; 16 x 16, 128 -> 128 75 -> 67 us; 2 groups of 20 -> 36 channels (narrow loads)
