@@ -48,6 +48,9 @@ BITS = {
     "13x13 groups": (64, 13, 13, 192, 3, 1, 1, 2, 260, ("fwd", "dgrad")),
     "13x13, 11 fragments": (64, 13, 13, 384, 3, 1, 1, 1, 200, ("fwd",)),
     "13x13, 11 fragments, back": (384, 13, 13, 64, 3, 1, 1, 1, 200, ("dgrad",)),
+    "22x22, 11 fragments": (32, 22, 22, 192, 3, 1, 1, 1, 150, ("fwd",)),
+    "12x15, 384 rows": (64, 12, 15, 384, 2, 1, 1, 1, 400, ("fwd",)),
+    "8x11, 256 rows, back": (256, 8, 11, 32, 3, 1, 1, 1, 400, ("dgrad",)),
     "1x1": (256, 32, 32, 64, 1, 1, 0, 1, 100, ("dgrad",)),
     "stride 2": (64, 17, 16, 64, 3, 2, 1, 1, 300, ("dgrad",)),
     "stride 2 5x5": (20, 19, 22, 64, 5, 2, 2, 1, 300, ("dgrad",)),
